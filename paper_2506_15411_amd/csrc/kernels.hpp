@@ -191,16 +191,36 @@ struct CbsArgs {
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
 constexpr int round64(int t) { return (t + 63) / 64 * 64; }
 
-// Rows per x-pass workgroup: TM threads serve one row.  The iteration kernel
-// needs about 200 VGPRs (two waves per SIMD), so workgroups of at most two
-// waves pack the CU fully; among R = 1..8 with R TM <= 128 pick the one whose
-// lanes fill their waves best, the larger R on ties (measured: 621 = 27 x 23
-// best at R = 4, 275 = 25 x 11 at R = 5; three-wave groups of R = 7 lose a
-// quarter of the occupancy and run 10% slower).
-constexpr int k1_rows_for(int tm) {
-  int best = 1;
-  for (int r = 2; r <= 8 && r * tm <= 128; ++r)
-    if (r * tm * round64(best * tm) >= best * tm * round64(r * tm)) best = r;
+// Rows per x-pass workgroup.  A row of n = N1 N2 is N2 tasks of level A
+// (DFT-N1, inverse and forward) and N1 tasks of level B (DFT-N2 twice and the
+// update); R rows pack their R N2 and R N1 tasks onto whole waves.  The rule
+// takes the R <= 8 with the least vector work per row, the waves of each level
+// weighed by its operation count (an n-point codelet about n times the sum of
+// its prime factors, the update about 25 per element), the larger R (longer
+// pieces of W) on ties.  Workgroups are at most four waves; two where a thread
+// holds more than about 160 registers (two waves per SIMD), since a larger
+// group then leaves part of the CU empty.  Measured, x pass in us (rows: time):
+// 189 = 27 x 7: 4: 99, 5: 110, 6: 96, 7: 87, 8: 96; 315 = 35 x 9: 3: 262, 5: 241,
+// 7: 226, 8: 478; 275 = 25 x 11: 4: 574, 5: 537, 7: 576; 261 = 29 x 9 (177
+// registers): 4: 207, 7: 235; 621 = 27 x 23 (197): 4: 605, 7: 640, 8: 627.
+constexpr int codelet_ops(int n) {
+  int ops = 0, m = n;
+  for (int p = 2; m > 1; ++p)
+    for (; m % p == 0; m /= p) ops += p;
+  return n * ops;
+}
+constexpr int k1_rows_for(int n1, int n2) {
+  const int regs = 2 * n1 * (n1 >= 17 && ct_is_prime(n1) ? 2 : 1) + 6 * n2;
+  const int most = regs > 160 ? 128 : 256;
+  const int wa = 2 * codelet_ops(n1), wb = 2 * codelet_ops(n2) + 25 * n2;
+  int best = 1, cost = wa * (round64(n2) / 64) + wb * (round64(n1) / 64);
+  for (int r = 2; r <= 8 && r * cmax(n1, n2) <= most; ++r) {
+    const int c = wa * (round64(r * n2) / 64) + wb * (round64(r * n1) / 64);
+    if (c * best <= cost * r) {
+      best = r;
+      cost = c;
+    }
+  }
   return best;
 }
 // Columns per z-pass workgroup: a whole brick row (8) unless the exchange
@@ -220,9 +240,8 @@ constexpr int kz_tx_for(int n1, int n2) {
 template <int N1, int N2>
 struct XGeom {
   static constexpr int N = N1 * N2;
-  static constexpr int TM = cmax(N1, N2);
-  static constexpr int LINES = k1_rows_for(TM);
-  static constexpr int THREADS = round64(LINES * TM);
+  static constexpr int LINES = k1_rows_for(N1, N2);
+  static constexpr int THREADS = round64(LINES * cmax(N1, N2));
 };
 template <int N1, int N2, int TX>
 struct YGeom {
@@ -324,7 +343,7 @@ template <int N1, int N2, int MODE, bool OBL>
 __global__ void __launch_bounds__((XGeom<N1, N2>::THREADS))
 k1_xpass(CbsArgs a) {
   using G = XGeom<N1, N2>;
-  constexpr int N = G::N, TM = G::TM, R = G::LINES;
+  constexpr int N = G::N, R = G::LINES;
   __shared__ float2 lds[R * N];     // R rows of one component, natural x order
   __shared__ double red[2 * (G::THREADS / 64)];
 
@@ -350,11 +369,16 @@ k1_xpass(CbsArgs a) {
   const int y0 = yg * R;
   const int rv = (a.ny - y0) < R ? (a.ny - y0) : R;   // valid rows in this group
 
-  const int t = tid % TM;
-  const int line = tid / TM;
-  const bool ok = (line < rv);
+  // The two levels of a row are different tasks: R N2 level-A tasks (row, j2),
+  // R N1 level-B tasks (row, k1), each packed onto the first lanes of the
+  // work-group, so waves without a task skip the level.
+  const int ta = tid % N2, la = tid / N2;   // level A: j2, row
+  const int t = tid % N1, line = tid / N1;  // level B: k1, row
+  const bool oka = la < rv;
+  const bool ok = line < rv;
   const int y = y0 + (ok ? line : 0);
-  float2* Lr = lds + (line < R ? line : 0) * N;
+  float2* La = lds + (oka ? la : 0) * N;
+  float2* Lr = lds + (ok ? line : 0) * N;
   // W bricks of this (component, z, row group): brick xt starts at wb + xt * ny * 8
   float2* wb = a.W + ib * a.sWb + c * a.sW + ((long long)z * a.gx * a.ny + y0) * kBrick;
   const long long bstride = (long long)a.ny * kBrick;
@@ -369,19 +393,19 @@ k1_xpass(CbsArgs a) {
   const float2* v0t = a.V0 + vbase + t;   // this thread's elements are t + N1 m
   float2* et = a.E + ebase + t;
   if constexpr (PF) {
-    if (ok && t < N1) {
+    if (ok) {
       sfor<0, N2>([&](auto M) { pv[CV(M)] = v0t[N1 * CV(M)]; });
       sfor<0, N2>([&](auto M) { pe[CV(M)] = et[N1 * CV(M)]; });
     }
   }
 
   // element x of this thread's row in the bricks
-  float2* wrow = wb + line * kBrick;
+  float2* wrow = wb + la * kBrick;
   auto wat = [&](int x) -> float2& { return wrow[(x / kBrick) * bstride + (x % kBrick)]; };
   // inverse level A input: thread j2 = t < N2 holds row[j2 + N2 j1]
   float2 b[N1];
   auto load_a = [&]() {
-    if (ok && t < N2) sfor<0, N1>([&](auto J1) { b[CV(J1)] = wat(t + N2 * CV(J1)); });
+    if (oka) sfor<0, N1>([&](auto J1) { b[CV(J1)] = wat(ta + N2 * CV(J1)); });
   };
   if constexpr (MODE != K1_FWD) load_a();
   tws.commit(tw, tid);
@@ -390,15 +414,15 @@ k1_xpass(CbsArgs a) {
 
   if constexpr (MODE != K1_FWD) {
     // inverse level A: DFT-N1 over row[j2 + N2 j1]
-    if (ok && t < N2) {
+    if (oka) {
       dft<N1, +1>(b);
-      const float2* twt = tw + t * N1;   // exp(-2 pi i t k1 / N), conjugated below
+      const float2* twt = tw + ta * N1;   // exp(-2 pi i j2 k1 / N), conjugated below
       sfor<0, N1>([&](auto K1) { b[CV(K1)] = cmulc(b[CV(K1)], twt[CV(K1)]); });
-      sfor<0, N1>([&](auto K1) { Lr[t + N2 * CV(K1)] = b[CV(K1)]; });
+      sfor<0, N1>([&](auto K1) { La[ta + N2 * CV(K1)] = b[CV(K1)]; });
     }
     __syncthreads();
     // inverse level B: thread k1 = t < N1, DFT-N2 over Lr[N2 k1 + j2]
-    if (ok && t < N1) {
+    if (ok) {
       sfor<0, N2>([&](auto J2) { v[CV(J2)] = Lr[N2 * t + CV(J2)]; });
       dft<N2, +1>(v);
     }
@@ -406,14 +430,14 @@ k1_xpass(CbsArgs a) {
   }
 
   if constexpr (MODE == K1_INV) {
-    if (ok && t < N1) {
+    if (ok) {
       sfor<0, N2>([&](auto M) { a.fout[ebase + t + N1 * CV(M)] = v[CV(M)]; });
     }
     return;
   }
 
   double sd = 0.0, se = 0.0;
-  if (ok && t < N1) {
+  if (ok) {
     const bool yin = (y >= a.py) && (y < a.ny - a.py);
     const bool zin = (z >= a.pz) && (z < a.nz - a.pz);
     // pol_c exp(i (ky y + kz z)); the x phase joins per element when oblique
@@ -474,10 +498,10 @@ k1_xpass(CbsArgs a) {
   __syncthreads();
   // forward level B': thread k1' = t < N2, DFT-N1 over Lr[N1 k1' + j2']
   float2 bo[N1];
-  if (ok && t < N2) {
-    sfor<0, N1>([&](auto J) { bo[CV(J)] = Lr[N1 * t + CV(J)]; });
+  if (oka) {
+    sfor<0, N1>([&](auto J) { bo[CV(J)] = La[N1 * ta + CV(J)]; });
     dft<N1, -1>(bo);
-    sfor<0, N1>([&](auto K) { wat(t + N2 * CV(K)) = bo[CV(K)]; });
+    sfor<0, N1>([&](auto K) { wat(ta + N2 * CV(K)) = bo[CV(K)]; });
   }
   if constexpr (MODE == K1_ITER) {
     const long long slot = (long long)ib * a.k1_blocks + (long long)rest * 3 + c;
@@ -751,7 +775,7 @@ struct SizeOps {
   LaunchKZ kz;        // z axis (nullptr: unsupported on z)
   int n1, n2;         // split of the x/y passes (twiddle table layout)
   int z1, z2;         // split of the z pass
-  int k1_rows;        // rows per x-pass workgroup when this length is the x axis
+  int k1_rows;         // rows per x-pass workgroup when this length is the x axis
 };
 
 constexpr int kTY = kBrick;   // columns per y-pass block
