@@ -882,13 +882,20 @@ int check_opts(const cbs_opts* o) {
   return CBS_OK;
 }
 
-// one CBS iteration: y forward, z forward + Green + z inverse, y inverse,
-// x inverse + update + next forward x, residual
-int enqueue_iteration(cbs_plan_s* p, const CbsArgs& a) {
+// prologue of a loop of iterations: W = V E + S (mode K1_FWD), x and y forward
+void enqueue_prologue(cbs_plan_s* p, const CbsArgs& a) {
+  p->ox->k1(a, K1_FWD, p->stream);
   p->oy->ky(a, -1, p->stream);
-  p->oz->kz(a, p->stream);
+}
+
+// one CBS iteration on W's x and y spectra: z forward + Green + z inverse, y
+// inverse, x inverse + update + next forward x, and the next forward y unless
+// no iteration follows (last)
+int enqueue_iteration(cbs_plan_s* p, const CbsArgs& a, bool last) {
+  p->oz->kz(a, p->stream);            // also reduces the iteration before's residual
   p->oy->ky(a, +1, p->stream);
-  p->ox->k1(a, K1_ITER, p->stream);   // its residual is reduced by the next y pass
+  p->ox->k1(a, K1_ITER, p->stream);
+  if (!last) p->oy->ky(a, -1, p->stream);
   HIP_LAUNCHED();
   return CBS_OK;
 }
@@ -943,7 +950,7 @@ int begin_solve(cbs_plan_s* p, CbsArgs& a, const cbs_opts* o, const cbs_source* 
   if (int rc = enqueue_solve_start(p, a, o, src, E_fwd, kv)) return rc;
   const bool plane = a.src == SRC_PLANE;
   HIP_TRY(hipEventRecord(p->ev0, p->stream));
-  p->ox->k1(a, K1_FWD, p->stream);
+  enqueue_prologue(p, a);
   HIP_LAUNCHED();
   A.on = true;
   A.stopped = false;
@@ -969,7 +976,7 @@ int advance_solve(cbs_plan_s* p, int iters) {
     return fail(CBS_E_STATE, "%d quanta already outstanding; poll before advancing", A.count);
   const int q = std::min(iters, A.max_iter - A.enqueued);
   for (int i = 0; i < q; ++i) {
-    int rc = enqueue_iteration(p, A.args);
+    int rc = enqueue_iteration(p, A.args, A.enqueued + i + 1 >= A.max_iter);
     if (rc != CBS_OK) return rc;
   }
   A.enqueued += q;
@@ -1179,7 +1186,7 @@ int run_static(cbs_plan_s* p, CbsArgs& a, const cbs_opts* o, const cbs_source* s
                const Kvec& kv, cbs_stats* stats) {
   const auto t0 = std::chrono::steady_clock::now();
   if (int rc = enqueue_solve_start(p, a, o, src, nullptr, kv)) return rc;
-  p->ox->k1(a, K1_FWD, p->stream);
+  enqueue_prologue(p, a);
   HIP_LAUNCHED();
   DevState hs;
   std::memset(&hs, 0, sizeof(hs));
@@ -1187,7 +1194,7 @@ int run_static(cbs_plan_s* p, CbsArgs& a, const cbs_opts* o, const cbs_source* s
   for (;;) {
     const int q = std::min(o->check_every, o->max_iter - enqueued);
     for (int i = 0; i < q; ++i)
-      if (int rc = enqueue_iteration(p, a)) return rc;
+      if (int rc = enqueue_iteration(p, a, enqueued + i + 1 >= o->max_iter)) return rc;
     enqueued += q;
     if (int rc = enqueue_residual(p, a)) return rc;
     HIP_TRY(hipMemcpyAsync(&hs, p->state, sizeof(DevState), hipMemcpyDeviceToHost, p->stream));
@@ -1724,25 +1731,26 @@ int cbs_time_passes(cbs_plan_t p, void* E_dev, int iters, float* ms_out) {
                      p->nx, p->ny, p->nz, kv);
   hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, p->stream, p->state, 0.0, iters, 0);
   HIP_LAUNCHED();
-  p->ox->k1(a, K1_FWD, p->stream);
+  enqueue_prologue(p, a);
+  constexpr int kSlot[5] = {1, 2, 3, 0, 4};   // launch order -> place in ms_out
   double acc[5] = {0, 0, 0, 0, 0};
   for (int it = 0; it < iters; ++it) {
     HIP_TRY(hipEventRecord(p->evp[0], p->stream));
-    p->oy->ky(a, -1, p->stream);
+    p->oz->kz(a, p->stream);   // reduces the residual, as in a solve
     HIP_TRY(hipEventRecord(p->evp[1], p->stream));
-    p->oz->kz(a, p->stream);
-    HIP_TRY(hipEventRecord(p->evp[2], p->stream));
     p->oy->ky(a, +1, p->stream);
-    HIP_TRY(hipEventRecord(p->evp[3], p->stream));
+    HIP_TRY(hipEventRecord(p->evp[2], p->stream));
     p->ox->k1(a, K1_ITER, p->stream);
+    HIP_TRY(hipEventRecord(p->evp[3], p->stream));
+    p->oy->ky(a, -1, p->stream);
     HIP_TRY(hipEventRecord(p->evp[4], p->stream));
-    HIP_LAUNCHED();   // the next y pass reduces the residual, as in a solve
+    HIP_LAUNCHED();
     HIP_TRY(hipEventRecord(p->evp[5], p->stream));
     HIP_TRY(hipEventSynchronize(p->evp[5]));
     for (int k = 0; k < 5; ++k) {
       float ms = 0.f;
       HIP_TRY(hipEventElapsedTime(&ms, p->evp[k], p->evp[k + 1]));
-      acc[k] += ms;
+      acc[kSlot[k]] += ms;
     }
   }
   for (int k = 0; k < 5; ++k) ms_out[k] = (float)(acc[k] / iters);
@@ -1983,8 +1991,8 @@ int enqueue_operator(const Scpml& s, const float2* v, float2* w) {
   a.fin = s.F;
   a.src_scale = 1.0f;   // F is already in units of the pitch
   a.warm = 1;
-  p->ox->k1(a, K1_FWD, p->stream);
-  if ((rc = enqueue_iteration(p, a))) return rc;
+  enqueue_prologue(p, a);
+  if ((rc = enqueue_iteration(p, a, true))) return rc;
   hipLaunchKernelGGL(k_gm_rsub, g, dim3(kGmThreads), 0, p->stream, v, w, s.n3);
   HIP_LAUNCHED();
   return CBS_OK;
@@ -2177,8 +2185,8 @@ int cbs_solve_scpml(cbs_plan_t p, const cbs_source* src, void* E_dev, const cbs_
   if ((rc = enqueue_solve_start(p, a, &so, src, nullptr, kv))) return rc;
   a.E = s.b;
   a.warm = 0;
-  p->ox->k1(a, K1_FWD, p->stream);
-  if ((rc = enqueue_iteration(p, a))) return rc;
+  enqueue_prologue(p, a);
+  if ((rc = enqueue_iteration(p, a, true))) return rc;
   float2* x = static_cast<float2*>(E_dev);
   dim3 gg;
   gm_grid(s.n3, gg);

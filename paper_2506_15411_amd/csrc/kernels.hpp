@@ -4,14 +4,17 @@
 //     W = V E_s + S;  GW = F^-1 G^ F W;  E_s += gamma (GW - E_s)
 // runs as four passes over HBM, each a batch of 1D FFTs along one axis:
 //
-//   KY(-)  forward FFT along y                               (W in place)
 //   KZ     forward FFT along z, G^(p) 3x3 multiply (1/N folded in),
 //          inverse FFT along z; all three components of a z-column
-//          are in one workgroup                              (W in place)
+//          are in one workgroup; one more workgroup reduces the
+//          residual partials of the iteration before        (W in place)
 //   KY(+)  inverse FFT along y                               (W in place)
 //   K1     inverse FFT along x -> GW, CBS update of E_s with FP64 residual
 //          partials, W = V E_s + S for the next iteration, forward FFT
 //          along x                                           (W, E_s)
+//   KY(-)  forward FFT along y, for the next iteration      (W in place)
+//
+// so the three passes that work within one z plane follow each other.
 //
 // Every 1D transform of length n = N1 * N2 is two register levels joined by
 // one exchange through LDS: level A does N2 DFT-N1 over stride-N2 subsets
@@ -77,9 +80,13 @@ struct DevState {
 // partials are summed in kResStreams interleaved streams (stream s takes
 // partials s, s + kResStreams, ... in order), the stream sums are combined by
 // one wave in a fixed order, so the result is the same double whichever kernel
-// and block shape runs it (the lagged reduction in the y pass and the
+// and block shape runs it (the lagged reduction in the z pass and the
 // quantum-end k_residual must agree bit for bit: which of them reduces a given
-// iteration depends on where the host's quanta end).  A batched solve has nb
+// iteration depends on where the host's quanta end).  A single work-group does
+// it, so its time is the latency of its loads: eight pairs of a thread are in
+// flight together (one at a time it was 50 us for the 18432 partials of
+// 192 x 192 x 256, longer than the y pass it then ran in; now under 10 us, in
+// the shadow of the pass's other work-groups: iteration 469 -> 432 us).  A batched solve has nb
 // illuminations with per_b partials each: each gets its own eta, and the solve
 // stops when the largest meets tol.  red holds 2 kResStreams doubles of LDS;
 // THREADS is any multiple of 64.
@@ -88,19 +95,39 @@ template <int THREADS>
 __device__ __forceinline__ void residual_finish(const double* part, int per_b, int nb,
                                                 DevState* st, double* hist, double* red) {
   static_assert(THREADS % 64 == 0, "whole waves");
+  typedef double pair_t __attribute__((ext_vector_type(2)));
+  constexpr int NS = (kResStreams + THREADS - 1) / THREADS;   // streams of a thread
+  constexpr int U = NS >= 4 ? 2 : 8 / NS;                     // partials of each in flight
   double eta = 0.0;      // the largest eta (meaningful in thread 0)
   bool bad = false;      // a non-finite eta
   for (int ib = 0; ib < nb; ++ib) {
-    const double* pb = part + 2LL * ib * per_b;
-    for (int s = threadIdx.x; s < kResStreams; s += THREADS) {
-      double a = 0.0, b = 0.0;
-      for (int i = s; i < per_b; i += kResStreams) {
-        a += __builtin_nontemporal_load(pb + 2 * i);
-        b += __builtin_nontemporal_load(pb + 2 * i + 1);
-      }
-      red[s] = a;
-      red[kResStreams + s] = b;
+    const pair_t* pb = reinterpret_cast<const pair_t*>(part) + (long long)ib * per_b;
+    double a[NS], b[NS];
+    sfor<0, NS>([&](auto Q) { a[CV(Q)] = b[CV(Q)] = 0.0; });
+    for (int i0 = threadIdx.x; i0 < per_b; i0 += U * kResStreams) {
+      pair_t v[U][NS];
+      sfor<0, U>([&](auto J) {
+        sfor<0, NS>([&](auto Q) {
+          const int s = threadIdx.x + CV(Q) * THREADS;
+          const int i = i0 + CV(Q) * THREADS + CV(J) * kResStreams;
+          v[CV(J)][CV(Q)] = pair_t{0.0, 0.0};
+          if (s < kResStreams && i < per_b) v[CV(J)][CV(Q)] = __builtin_nontemporal_load(pb + i);
+        });
+      });
+      sfor<0, U>([&](auto J) {
+        sfor<0, NS>([&](auto Q) {
+          a[CV(Q)] += v[CV(J)][CV(Q)].x;
+          b[CV(Q)] += v[CV(J)][CV(Q)].y;
+        });
+      });
     }
+    sfor<0, NS>([&](auto Q) {
+      const int s = threadIdx.x + CV(Q) * THREADS;
+      if (s < kResStreams) {
+        red[s] = a[CV(Q)];
+        red[kResStreams + s] = b[CV(Q)];
+      }
+    });
     __syncthreads();
     if (threadIdx.x < 64) {
       const int l = threadIdx.x;
@@ -523,20 +550,6 @@ ky_pass(CbsArgs a) {
   if (a.st->done) return;
   const int tid = threadIdx.x;
   if (a.ky_prio) __builtin_amdgcn_s_setprio(kLoadPrio);
-  if (S < 0 && blockIdx.x == 0 && a.st->pending) {
-    // finish the previous iteration's residual (stream order: the x pass that
-    // wrote the partials has completed); lds is still unused here
-    constexpr bool kFits = sizeof(lds) >= 2 * kResStreams * sizeof(double);
-    if constexpr (kFits) {
-      residual_finish<G::THREADS>(a.partials, a.k1_blocks, a.nb, a.st, a.hist,
-                                  reinterpret_cast<double*>(lds));
-    } else {
-      __shared__ double red[2 * kResStreams];
-      residual_finish<G::THREADS>(a.partials, a.k1_blocks, a.nb, a.st, a.hist, red);
-    }
-    if (tid == 0) a.st->pending = 0;
-    __syncthreads();
-  }
   TwStage<N, G::THREADS> tws;
   tws.issue(a.twy, tid);
   const int xi = tid % TX;
@@ -601,6 +614,22 @@ kz_pass(CbsArgs a) {
   __shared__ float2 lds[3 * N * TX];
   __shared__ float2 tw[N];
   if (a.st->done) return;
+  // block 0 transforms nothing: it finishes the previous iteration's residual
+  // (stream order: the x pass that wrote the partials has completed) beside the
+  // columns of the others
+  if (blockIdx.x == 0) {
+    if (!a.st->pending) return;
+    constexpr bool kFits = sizeof(lds) >= 2 * kResStreams * sizeof(double);
+    if constexpr (kFits) {
+      residual_finish<G::THREADS>(a.partials, a.k1_blocks, a.nb, a.st, a.hist,
+                                  reinterpret_cast<double*>(lds));
+    } else {
+      __shared__ double red[2 * kResStreams];
+      residual_finish<G::THREADS>(a.partials, a.k1_blocks, a.nb, a.st, a.hist, red);
+    }
+    if (threadIdx.x == 0) a.st->pending = 0;
+    return;
+  }
   const int tid = threadIdx.x;
   TwStage<N, G::THREADS> tws;
   tws.issue(a.twz, tid);
@@ -611,7 +640,7 @@ kz_pass(CbsArgs a) {
   static_assert(kBrick % TX == 0, "z-pass tiles split a brick row evenly");
   constexpr int PARTS = kBrick / TX;
   const unsigned per_b = (unsigned)(a.nxp / TX) * (unsigned)a.ny;
-  const unsigned Lb = xcd_remap(blockIdx.x, per_b * (unsigned)a.nb);
+  const unsigned Lb = xcd_remap(blockIdx.x - 1, per_b * (unsigned)a.nb);
   const int ib = (int)(Lb / per_b);
   const unsigned L = Lb - (unsigned)ib * per_b;
   const int part = (int)(L % PARTS);
@@ -849,7 +878,7 @@ template <int N1, int N2>
 void launch_kz(const CbsArgs& a, hipStream_t s) {
   constexpr int TX = kz_tx_for(N1, N2);
   using G = ZGeom<N1, N2, TX>;
-  dim3 grid((unsigned)((long long)(a.nxp / TX) * a.ny * a.nb));
+  dim3 grid((unsigned)((long long)(a.nxp / TX) * a.ny * a.nb) + 1);   // + the residual's block
   hipLaunchKernelGGL((kz_pass<N1, N2, TX>), grid, dim3(G::THREADS), 0, s, a);
 }
 
