@@ -226,7 +226,8 @@ constexpr int round64(int t) { return (t + 63) / 64 * 64; }
 // its prime factors, the update about 25 per element), the larger R (longer
 // pieces of W) on ties.  Workgroups are at most four waves; two where a thread
 // holds more than about 160 registers (two waves per SIMD), since a larger
-// group then leaves part of the CU empty.  Measured, x pass in us (rows: time):
+// group then leaves part of the CU empty.  Measured on these splits, x pass in
+// us (rows: time):
 // 189 = 27 x 7: 4: 99, 5: 110, 6: 96, 7: 87, 8: 96; 315 = 35 x 9: 3: 262, 5: 241,
 // 7: 226, 8: 478; 275 = 25 x 11: 4: 574, 5: 537, 7: 576; 261 = 29 x 9 (177
 // registers): 4: 207, 7: 235; 621 = 27 x 23 (197): 4: 605, 7: 640, 8: 627.
