@@ -360,7 +360,9 @@ int cbs_history(cbs_plan_t plan, double* out_host, int max);
  * plan's stream between the passes, and return the mean device time per
  * launch in ms_out[0..4] = { y forward, z (forward + Green + inverse),
  * y inverse, x (inverse + update + forward), residual } (the residual
- * reduction runs inside the next z pass; ms_out[4] is then 0).
+ * reduction runs inside the next z pass; ms_out[4] is then 0).  Where the
+ * y and x passes of a plane run as one kernel, its time is the x entry and
+ * the y entries are 0.
  * Synchronises. */
 int cbs_time_passes(cbs_plan_t plan, void* E_dev, int iters, float* ms_out);
 

@@ -825,6 +825,26 @@ int set_permittivity_impl(cbs_plan_s* p, const void* eps_r, int dtype) {
   return CBS_OK;
 }
 
+// Whether the fused plane pass runs instead of the three passes of a plane:
+// square planes that fit in LDS, enough of them to occupy the CUs.  A plane's
+// time does not depend on how many there are until every CU has one, the three
+// passes' does: up to 64 x 64 the fused pass wins from 12 planes on (64 x 64 x 4:
+// 12.5 us an iteration against 15.2), above that from about N^2 / 192 planes
+// (96^2: 36 planes 21.4 against 21.3 us; 121^2: 60 planes 38.6 against 35.4, 72
+// planes 40.0 against 39.1; 128^2: 60 planes 34.4 against 35.0).  The number of
+// illuminations does not enter, so a batch takes the path of its single solves.
+bool plane_fused(const cbs_plan_s* p) {
+  const int n = p->nx;
+  return n == p->ny && p->ox->kxy && (n <= 64 || 3LL * p->nz * 192 >= (long long)n * n);
+}
+
+// the number of illuminations and what follows from it
+void set_illuminations(const cbs_plan_s* p, CbsArgs& a, int nb) {
+  a.nb = nb;
+  a.fused = plane_fused(p) ? 1 : 0;
+  a.k1_blocks = a.fused ? 3 * p->nz : p->k1_blocks;
+}
+
 CbsArgs base_args(cbs_plan_s* p) {
   CbsArgs a;
   std::memset(&a, 0, sizeof(a));
@@ -846,8 +866,7 @@ CbsArgs base_args(cbs_plan_s* p) {
   a.twz = p->twz;
   a.phase = p->phase;
   a.partials = p->partials;
-  a.k1_blocks = p->k1_blocks;
-  a.nb = 1;
+  set_illuminations(p, a, 1);
   a.sWb = 3 * a.sW;
   a.sEb = 3 * a.sE;
   a.phx = p->phx;
@@ -890,9 +909,14 @@ void enqueue_prologue(cbs_plan_s* p, const CbsArgs& a) {
 
 // one CBS iteration on W's x and y spectra: z forward + Green + z inverse, y
 // inverse, x inverse + update + next forward x, and the next forward y unless
-// no iteration follows (last)
+// no iteration follows (last); the plane's three in one launch where fused
 int enqueue_iteration(cbs_plan_s* p, const CbsArgs& a, bool last) {
   p->oz->kz(a, p->stream);            // also reduces the iteration before's residual
+  if (a.fused) {
+    p->ox->kxy(a, p->stream);
+    HIP_LAUNCHED();
+    return CBS_OK;
+  }
   p->oy->ky(a, +1, p->stream);
   p->ox->k1(a, K1_ITER, p->stream);
   if (!last) p->oy->ky(a, -1, p->stream);
@@ -1459,7 +1483,7 @@ int cbs_solve_batch(cbs_plan_t p, int count, const cbs_source* srcs, void* E_dev
     if ((rc = set_plane_wave(p, a, kv, b, &srcs[b]))) return rc;
   }
   char* base = static_cast<char*>(work);
-  a.nb = count;
+  set_illuminations(p, a, count);
   a.W = reinterpret_cast<float2*>(base + B.W);
   a.partials = reinterpret_cast<double*>(base + B.partials);
   a.phx = reinterpret_cast<float2*>(base + B.phx);
@@ -1738,11 +1762,14 @@ int cbs_time_passes(cbs_plan_t p, void* E_dev, int iters, float* ms_out) {
     HIP_TRY(hipEventRecord(p->evp[0], p->stream));
     p->oz->kz(a, p->stream);   // reduces the residual, as in a solve
     HIP_TRY(hipEventRecord(p->evp[1], p->stream));
-    p->oy->ky(a, +1, p->stream);
+    if (!a.fused) p->oy->ky(a, +1, p->stream);
     HIP_TRY(hipEventRecord(p->evp[2], p->stream));
-    p->ox->k1(a, K1_ITER, p->stream);
+    if (a.fused)
+      p->ox->kxy(a, p->stream);
+    else
+      p->ox->k1(a, K1_ITER, p->stream);
     HIP_TRY(hipEventRecord(p->evp[3], p->stream));
-    p->oy->ky(a, -1, p->stream);
+    if (!a.fused) p->oy->ky(a, -1, p->stream);
     HIP_TRY(hipEventRecord(p->evp[4], p->stream));
     HIP_LAUNCHED();
     HIP_TRY(hipEventRecord(p->evp[5], p->stream));

@@ -192,8 +192,9 @@ struct CbsArgs {
   const float2* fin;            // FIELD source / Green input
   float2* fout;                 // Green output
   double* partials;             // 2 doubles per K1 block
-  int k1_blocks;                // K1 blocks per illumination (partials to reduce for each)
+  int k1_blocks;                // K1 or KXY blocks per illumination (partials to reduce)
   int nb;                       // illuminations advanced together (1: an ordinary solve)
+  int fused;                    // host: the plane's passes run as one (kxy)
   long long sWb, sEb;           // stride between illuminations in W (3 sW) and E (3 sE)
   const float2* phx;            // [nb][nx] exp(i kx d x) of each illumination's plane wave
   const float2* phy;            // [nb][ny] exp(i ky d y)
@@ -605,6 +606,222 @@ ky_pass(CbsArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// KXY: the three passes of one square plane in one
+// ---------------------------------------------------------------------------
+// A workgroup holds one (component, z) plane of N x N points in LDS and runs
+// KY(+), K1 and KY(-) on it: W crosses HBM once each way instead of three times.
+// Every level works in place, so a level needs one barrier and no second buffer:
+//   inverse A   task j2: points j2 + N2 j1, DFT-N1, twiddle, back to j2 + N2 k1
+//   inverse B   task k1: positions N2 k1 + j2, DFT-N2 -> points k1 + N1 m, left
+//               at N2 k1 + m
+//   forward A'  task k1: those positions (points k1 + N1 m), DFT-N2, twiddle
+//   forward B'  task k': positions N2 k1 + k', DFT-N1 -> k' + N2 K, natural order
+// along y (a column per task) and, between, along x (a row per task); the row at
+// position q holds y = q / N2 + N1 (q % N2) while the x levels run.
+//
+// One plane is one CU's work, and its time is the latency of seven dependent
+// levels (about 13 us at 64 x 64, 24 at 128 x 128), bounded by vector
+// instructions there (16 us of issue at 128 x 128).  Threads: as few as keep the
+// rounds of 1024 threads over the N N2 and N N1 tasks of the two levels (96 =
+// 12 x 8: 768 threads 34.5 us, 576 36.6; 121: 704 threads 61.5, 1024 79.5 with a
+// mostly empty second round).  Row pitch N + 8: rows then start 64 bytes apart in
+// the banks and stay 16-byte aligned (128: 56.2 us, N + 2 59.3, N + 1 65.3).
+// 512-thread groups are held to six waves per SIMD, so three planes share a CU
+// (64 x 64 x 256: 22.7 us against 26.9).  Iteration in us, three passes -> fused:
+// 16^3 14.5 -> 8.6, 32^3 16.4 -> 10.8, 64^3 29.5 -> 19.5, 96^3 52.6 -> 46.3,
+// 121^3 88.4 -> 82.3, 128^3 95.7 -> 77.7, 128 x 128 x 256 172.7 -> 133.
+template <int N1, int N2>
+struct XYGeom {
+  static constexpr int N = N1 * N2;
+  static constexpr int P = N % 2 ? N : N + 8;       // row pitch in LDS
+  static constexpr int GX = (N + kBrick - 1) / kBrick;
+  static constexpr int RA = (N * N2 + 1023) / 1024, RB = (N * N1 + 1023) / 1024;   // rounds
+  static constexpr int THREADS = round64(cmax((N * N2 + RA - 1) / RA, (N * N1 + RB - 1) / RB));
+  static constexpr int WAVES = THREADS == 512 ? 6 : 1;   // per SIMD, at least
+  static constexpr int QG = (GX * kBrick * N2 + THREADS - 1) / THREADS;   // columns x N2 tasks
+  static constexpr int QA = (N * N2 + THREADS - 1) / THREADS;
+  static constexpr int QB = (N * N1 + THREADS - 1) / THREADS;
+};
+template <int N1, int N2, bool OBL>
+__global__ void __launch_bounds__((XYGeom<N1, N2>::THREADS), (XYGeom<N1, N2>::WAVES))
+kxy_pass(CbsArgs a) {
+  using G = XYGeom<N1, N2>;
+  constexpr int N = G::N, P = G::P, T = G::THREADS;
+  __shared__ float2 lds[N * P];
+  __shared__ float2 tw[N];
+  __shared__ double red[2 * (T / 64)];
+  if (a.st->done) return;
+  const int tid = threadIdx.x;
+  TwStage<N, T> tws;
+  tws.issue(a.twx, tid);
+  // block -> (z, illumination, component), a z plane's components adjacent so
+  // they share V0 in one L2
+  const unsigned per = 3u * (unsigned)a.nb;
+  const unsigned L = xcd_remap(blockIdx.x, per * (unsigned)a.nz);
+  const int z = (int)(L / per);
+  const int cc = (int)(L % per);
+  const int ib = cc / 3, c = cc - 3 * ib;
+  float2* wp = a.W + ib * a.sWb + c * a.sW + (long long)z * G::GX * N * kBrick;
+  const float2* v0p = a.V0 + (long long)z * N * N;
+  const long long ebase = ib * a.sEb + c * a.sE + (long long)z * N * N;
+  float2* ep = a.E + ebase;
+
+  // inverse y, level A: task (xi, j2, brick), a wave reads whole brick rows
+  {
+    float2 b[G::QG][N1];
+    sfor<0, G::QG>([&](auto QQ) {
+      const int i = tid + CV(QQ) * T;
+      const int xi = i % kBrick, j2 = (i / kBrick) % N2, br = i / (kBrick * N2);
+      if (br * kBrick + xi < N) {
+        const float2* w = wp + ((long long)br * N + j2) * kBrick + xi;
+        sfor<0, N1>([&](auto J) { b[CV(QQ)][CV(J)] = w[N2 * kBrick * CV(J)]; });
+      }
+    });
+    tws.commit(tw, tid);
+    __syncthreads();
+    sfor<0, G::QG>([&](auto QQ) {
+      const int i = tid + CV(QQ) * T;
+      const int xi = i % kBrick, j2 = (i / kBrick) % N2, br = i / (kBrick * N2);
+      const int x = br * kBrick + xi;
+      if (x < N) {
+        dft<N1, +1>(b[CV(QQ)]);
+        const float2* t = tw + j2 * N1;
+        sfor<0, N1>([&](auto K) { lds[(j2 + N2 * CV(K)) * P + x] = cmulc(b[CV(QQ)][CV(K)], t[CV(K)]); });
+      }
+    });
+  }
+  // the pointwise operands of this thread's x-level-B tasks (y, k1): elements
+  // x = k1 + N1 m of row y, in flight during the levels before them
+  float2 pv[G::QB][N2], pe[G::QB][N2];
+  sfor<0, G::QB>([&](auto QQ) {
+    const int i = tid + CV(QQ) * T;
+    if (i < N * N1) {
+      const int o = (i / N1) * N + i % N1;
+      sfor<0, N2>([&](auto M) { pv[CV(QQ)][CV(M)] = v0p[o + N1 * CV(M)]; });
+      sfor<0, N2>([&](auto M) { pe[CV(QQ)][CV(M)] = ep[o + N1 * CV(M)]; });
+    }
+  });
+  __syncthreads();
+  // inverse y, level B: task (x, k1)
+  sfor<0, G::QB>([&](auto QQ) {
+    const int i = tid + CV(QQ) * T;
+    if (i < N * N1) {
+      float2* l = lds + N2 * (i / N) * P + i % N;
+      float2 v[N2];
+      sfor<0, N2>([&](auto J) { v[CV(J)] = l[CV(J) * P]; });
+      dft<N2, +1>(v);
+      sfor<0, N2>([&](auto J) { l[CV(J) * P] = v[CV(J)]; });
+    }
+  });
+  __syncthreads();
+  // inverse x, level A: task (row, j2)
+  sfor<0, G::QA>([&](auto QQ) {
+    const int i = tid + CV(QQ) * T;
+    if (i < N * N2) {
+      const int j2 = i % N2;
+      float2* l = lds + (i / N2) * P + j2;
+      float2 b[N1];
+      sfor<0, N1>([&](auto J) { b[CV(J)] = l[N2 * CV(J)]; });
+      dft<N1, +1>(b);
+      const float2* t = tw + j2 * N1;
+      sfor<0, N1>([&](auto K) { l[N2 * CV(K)] = cmulc(b[CV(K)], t[CV(K)]); });
+    }
+  });
+  __syncthreads();
+  // inverse x, level B; update; W = V E_s + S; forward x, level A'
+  const bool zin = (z >= a.pz) && (z < a.nz - a.pz);
+  const float2 ph = a.phase[(ib * 3 + c) * a.nz + z];   // pol_c exp(i kz z)
+  double sd = 0.0, se = 0.0;
+  sfor<0, G::QB>([&](auto QQ) {
+    const int i = tid + CV(QQ) * T;
+    if (i < N * N1) {
+      const int t = i % N1, y = i / N1;
+      const int o = y * N + t;
+      float2* l = lds + (N2 * (y % N1) + y / N1) * P + N2 * t;
+      float2 v[N2];
+      sfor<0, N2>([&](auto J) { v[CV(J)] = l[CV(J)]; });
+      dft<N2, +1>(v);
+      const bool yzin = zin && (y >= a.py) && (y < a.ny - a.py);
+      const float2 spl = OBL ? cmul(ph, a.phy[ib * a.ny + y]) : ph;
+      const float2* phxb = a.phx + ib * a.nx;
+      sfor<0, N2>([&](auto M) {
+        const int x = t + N1 * CV(M);
+        const float2 v0 = pv[CV(QQ)][CV(M)];
+        float2 e = pe[CV(QQ)][CV(M)];
+        const float2 gm = make_float2(1.0f - v0.y * a.inv_eps, v0.x * a.inv_eps);
+        const float2 d = cmul(gm, csub(v[CV(M)], e));
+        e = cadd(e, d);
+        sd += (double)(d.x * d.x + d.y * d.y);
+        se += (double)(e.x * e.x + e.y * e.y);
+        ep[o + N1 * CV(M)] = e;
+        float2 w = cmul(make_float2(v0.x, v0.y - a.eps), e);
+        if (a.src == SRC_PLANE) {
+          if (yzin && (x >= a.px) && (x < a.nx - a.px)) {
+            if constexpr (OBL)
+              w = cadd(w, cmul(v0, cmul(spl, phxb[x])));
+            else
+              w = cadd(w, cmul(v0, spl));
+          }
+        } else if (a.src == SRC_FIELD) {
+          w = cadd(w, cscale(a.fin[ebase + o + N1 * CV(M)], a.src_scale));
+        } else if (a.src == SRC_FIELD_CONJ) {
+          const float2 f = a.fin[ebase + o + N1 * CV(M)];
+          w = cadd(w, make_float2(f.x * a.src_scale, -f.y * a.src_scale));
+        } else if (a.src == SRC_POINT) {
+          if (x == a.r0x && y == a.r0y && z == a.r0z) w = cadd(w, a.st->amp[c]);
+        }
+        v[CV(M)] = w;
+      });
+      dft<N2, -1>(v);
+      const float2* tc = tw + t;
+      sfor<0, N2>([&](auto K) { l[CV(K)] = cmul(v[CV(K)], tc[N1 * CV(K)]); });
+    }
+  });
+  __syncthreads();
+  // forward x, level B': task (row, k')
+  sfor<0, G::QA>([&](auto QQ) {
+    const int i = tid + CV(QQ) * T;
+    if (i < N * N2) {
+      float2* l = lds + (i / N2) * P + i % N2;
+      float2 b[N1];
+      sfor<0, N1>([&](auto J) { b[CV(J)] = l[N2 * CV(J)]; });
+      dft<N1, -1>(b);
+      sfor<0, N1>([&](auto K) { l[N2 * CV(K)] = b[CV(K)]; });
+    }
+  });
+  __syncthreads();
+  // forward y, level A': task (x, k1)
+  sfor<0, G::QB>([&](auto QQ) {
+    const int i = tid + CV(QQ) * T;
+    if (i < N * N1) {
+      const int t = i / N;
+      float2* l = lds + N2 * t * P + i % N;
+      float2 v[N2];
+      sfor<0, N2>([&](auto J) { v[CV(J)] = l[CV(J) * P]; });
+      dft<N2, -1>(v);
+      const float2* tc = tw + t;
+      sfor<0, N2>([&](auto K) { l[CV(K) * P] = cmul(v[CV(K)], tc[N1 * CV(K)]); });
+    }
+  });
+  __syncthreads();
+  // forward y, level B': task (xi, k', brick), written straight to the bricks
+  sfor<0, G::QG>([&](auto QQ) {
+    const int i = tid + CV(QQ) * T;
+    const int xi = i % kBrick, k = (i / kBrick) % N2, br = i / (kBrick * N2);
+    const int x = br * kBrick + xi;
+    if (x < N) {
+      float2 b[N1];
+      sfor<0, N1>([&](auto J) { b[CV(J)] = lds[(N2 * CV(J) + k) * P + x]; });
+      dft<N1, -1>(b);
+      float2* w = wp + ((long long)br * N + k) * kBrick + xi;
+      sfor<0, N1>([&](auto K) { w[N2 * kBrick * CV(K)] = b[CV(K)]; });
+    }
+  });
+  block_sum2<T>(sd, se, red, a.partials + 2 * ((long long)ib * a.k1_blocks + (long long)z * 3 + c));
+  if (blockIdx.x == 0 && tid == 0) a.st->pending = 1;
+}
+
+// ---------------------------------------------------------------------------
 // KZ: FFT along z, Green's tensor, inverse FFT along z (3 components)
 // ---------------------------------------------------------------------------
 template <int N1, int N2, int TX>
@@ -800,6 +1017,7 @@ using LaunchKZ = void (*)(const CbsArgs&, hipStream_t);
 
 struct SizeOps {
   int n;
+  LaunchKZ kxy;       // the fused plane pass of an n x n plane (nullptr: none)
   LaunchK1 k1;        // x axis
   LaunchKY ky;        // y axis
   LaunchKZ kz;        // z axis (nullptr: unsupported on z)
@@ -883,13 +1101,31 @@ void launch_kz(const CbsArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((kz_pass<N1, N2, TX>), grid, dim3(G::THREADS), 0, s, a);
 }
 
+template <int N1, int N2>
+void launch_kxy(const CbsArgs& a, hipStream_t s) {
+  using G = XYGeom<N1, N2>;
+  const dim3 grid(3u * (unsigned)a.nb * (unsigned)a.nz);
+  if (a.oblique && a.src == SRC_PLANE)
+    hipLaunchKernelGGL((kxy_pass<N1, N2, true>), grid, dim3(G::THREADS), 0, s, a);
+  else
+    hipLaunchKernelGGL((kxy_pass<N1, N2, false>), grid, dim3(G::THREADS), 0, s, a);
+}
+// the fused plane pass needs a plane of N x N complex values in 160 KB of LDS
+template <int N1, int N2>
+constexpr LaunchKZ kxy_for() {
+  if constexpr (N2 > 1 && N1 * N2 <= 128)
+    return &launch_kxy<N1, N2>;
+  else
+    return nullptr;
+}
+
 #define CBS_SIZE_XYZ(n, a1, a2, z1, z2)                                                  \
   SizeOps {                                                                              \
-    n, &launch_k1<a1, a2>, &launch_ky<a1, a2>, &launch_kz<z1, z2>, a1, a2, z1, z2,       \
+    n, kxy_for<a1, a2>(), &launch_k1<a1, a2>, &launch_ky<a1, a2>, &launch_kz<z1, z2>, a1, a2, z1, z2,       \
         XGeom<a1, a2>::LINES                                                             \
   }
 #define CBS_SIZE_XY(n, a1, a2) \
-  SizeOps { n, &launch_k1<a1, a2>, &launch_ky<a1, a2>, nullptr, a1, a2, 0, 0, XGeom<a1, a2>::LINES }
+  SizeOps { n, nullptr, &launch_k1<a1, a2>, &launch_ky<a1, a2>, nullptr, a1, a2, 0, 0, XGeom<a1, a2>::LINES }
 
 // registry, defined in the size translation units
 const SizeOps* find_size(int n);
