@@ -1821,7 +1821,7 @@ int cbs_bandwidth_probe(const void* src, void* dst, size_t bytes, int reps, void
 namespace {
 
 struct ScpmlLayout {
-  size_t basis, b, F, X, Z, mats[3], cols[3], part, h, y, total;
+  size_t basis, b, F, u, sinv[3], part, h, y, total;
 };
 
 bool scpml_layout(int nx, int ny, int nz, int restart, ScpmlLayout& S) {
@@ -1839,11 +1839,8 @@ bool scpml_layout(int nx, int ny, int nz, int restart, ScpmlLayout& S) {
   S.basis = take((size_t)(restart + 1) * 3 * N * sizeof(float2));
   S.b = take(3 * N * sizeof(float2));
   S.F = take(3 * N * sizeof(float2));
-  S.X = take(N * sizeof(float2));
-  S.Z = take(N * sizeof(float2));
-  for (int a = 0; a < 3; ++a)
-    S.mats[a] = take((3 * (size_t)dims[a] * dims[a] + dims[a]) * sizeof(float2));
-  for (int a = 0; a < 3; ++a) S.cols[a] = take(5 * (size_t)dims[a] * sizeof(double2));
+  S.u = take(3 * N * sizeof(float2));
+  for (int a = 0; a < 3; ++a) S.sinv[a] = take((size_t)dims[a] * sizeof(float2));
   S.part = take((size_t)(kScpmlMaxRestart + 1) * kGmBlocks * sizeof(double2));
   S.h = take((size_t)3 * (kScpmlMaxRestart + 1) * sizeof(double2));
   S.y = take((size_t)(kScpmlMaxRestart + 1) * sizeof(double2));
@@ -1855,9 +1852,8 @@ struct Scpml {
   cbs_plan_s* p;
   int dims[3];
   long long N, n3;            // voxels; complex values of a vector field
-  float2 *basis, *b, *F, *X, *Z;
-  const float2 *A[3], *B[3], *T[3], *sinv[3];
-  bool thin[3];               // 8p <= n: A and B in the two-launch form (RA|CA, RB|CB)
+  float2 *basis, *b, *F, *u;
+  const float2* sinv[3];      // 1/s along each axis
   double2 *part, *h, *y;
   float2* vec(int i) const { return basis + (long long)i * n3; }
 };
@@ -1887,113 +1883,17 @@ int scpml_setup(cbs_plan_s* p, const cbs_scpml* layer, int restart, void* work, 
   s.basis = reinterpret_cast<float2*>(base + S.basis);
   s.b = reinterpret_cast<float2*>(base + S.b);
   s.F = reinterpret_cast<float2*>(base + S.F);
-  s.X = reinterpret_cast<float2*>(base + S.X);
-  s.Z = reinterpret_cast<float2*>(base + S.Z);
+  s.u = reinterpret_cast<float2*>(base + S.u);
   s.part = reinterpret_cast<double2*>(base + S.part);
   s.h = reinterpret_cast<double2*>(base + S.h);
   s.y = reinterpret_cast<double2*>(base + S.y);
   for (int a = 0; a < 3; ++a) {
     const int n = s.dims[a];
-    float2* m = reinterpret_cast<float2*>(base + S.mats[a]);
-    double2* col = reinterpret_cast<double2*>(base + S.cols[a]);
-    s.A[a] = m;
-    s.B[a] = m + (size_t)n * n;
-    s.T[a] = m + 2 * (size_t)n * n;
-    s.sinv[a] = m + 3 * (size_t)n * n;
-    hipLaunchKernelGGL(k_scpml_columns, dim3((n + 127) / 128), dim3(128), 0, p->stream, n,
-                       p->pml[a], layer->order, layer->alpha_max, col, col + n, col + 2 * n,
-                       col + 3 * n, col + 4 * n);
+    float2* si = reinterpret_cast<float2*>(base + S.sinv[a]);
+    s.sinv[a] = si;
+    hipLaunchKernelGGL(k_scpml_sinv, dim3((n + 127) / 128), dim3(128), 0, p->stream, n, p->pml[a],
+                       layer->order, layer->alpha_max, si);
     HIP_LAUNCHED();
-    const long long nn = (long long)n * n;
-    hipLaunchKernelGGL(k_scpml_matrices, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0,
-                       p->stream, n, p->pml[a], col, col + n, col + 2 * n, col + 3 * n,
-                       col + 4 * n, const_cast<float2*>(s.A[a]), const_cast<float2*>(s.B[a]),
-                       const_cast<float2*>(s.T[a]), const_cast<float2*>(s.sinv[a]));
-    HIP_LAUNCHED();
-    const int pa = p->pml[a];
-    s.thin[a] = pa > 0 && 8 * pa <= n;
-    if (s.thin[a]) {
-      const long long nt = 6LL * pa * n;
-      hipLaunchKernelGGL(k_scpml_thin, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0,
-                         p->stream, n, pa, col, col + n, col + 2 * n, col + 3 * n,
-                         const_cast<float2*>(s.A[a]), const_cast<float2*>(s.B[a]));
-      HIP_LAUNCHED();
-    }
-  }
-  return CBS_OK;
-}
-
-// one axis product (kMm* epilogues, see scpml.hpp) over scalar [nz][ny][nx] fields;
-// kMmCompact writes and kMmColFix reads the compact [lines][4p] buffer cbuf
-int enqueue_axis_mm(const Scpml& s, int axis, const float2* M, const float2* in, float2* out,
-                    float alpha, bool accumulate, int mode = kMmPlain, float2* out2 = nullptr,
-                    const float2* cbuf = nullptr) {
-  AxisMM a;
-  a.M = M;
-  a.in = in;
-  a.out = out;
-  a.out2 = out2;
-  a.sinv = s.sinv[axis];
-  a.aux = cbuf;
-  a.n = s.dims[axis];
-  a.Q = axis == 0 ? 1 : (axis == 1 ? s.dims[0] : s.dims[0] * s.dims[1]);
-  a.p = s.p->pml[axis];
-  a.rows = mode == kMmLayer ? 2 * a.p : (mode == kMmCompact ? 4 * a.p : a.n);
-  a.K = mode == kMmColFix ? 2 * a.p : a.n;
-  a.ldm = a.K;
-  a.cld = 4LL * a.p;
-  a.in_ld = mode == kMmColFix ? a.cld : 0;
-  a.L = s.N / a.n;
-  a.alpha = alpha;
-  a.accumulate = accumulate ? 1 : 0;
-  a.mode = mode;
-  if (a.rows <= 0 || a.K <= 0) return CBS_OK;
-  const unsigned tiles = (unsigned)((a.L + kMmTL - 1) / kMmTL) *
-                         (unsigned)((a.rows + kMmTI - 1) / kMmTI);
-  if (a.Q == 1 || a.in_ld > 0)
-    hipLaunchKernelGGL(k_axis_mm<true>, dim3(tiles), dim3(256), 0, s.p->stream, a);
-  else
-    hipLaunchKernelGGL(k_axis_mm<false>, dim3(tiles), dim3(256), 0, s.p->stream, a);
-  HIP_LAUNCHED();
-  return CBS_OK;
-}
-
-// F_c += alpha M v_c along axis b for M = A_b (B) or B_b (!A): one dense product,
-// or on a thin layer the two launches of the split form, with X as the compact
-// buffer (X is no longer needed once every (S^-1 - I) T_c X term is formed)
-int enqueue_ab(const Scpml& s, int b, bool A, const float2* vc, float2* Fc, float alpha) {
-  const float2* M = A ? s.A[b] : s.B[b];
-  if (!s.thin[b]) return enqueue_axis_mm(s, b, M, vc, Fc, alpha, true);
-  const long long rows4 = 4LL * s.p->pml[b] * s.dims[b];   // RA (4p x n), then CA (n x 2p)
-  if (int rc = enqueue_axis_mm(s, b, M, vc, s.X, 1.0f, false, kMmCompact)) return rc;
-  return enqueue_axis_mm(s, b, M + rows4, s.X, Fc, alpha, true, kMmColFix, nullptr, s.X);
-}
-
-// F = alpha (L_s - L) v:  per component c, sum_{b != c} A_b v_c + B_c v_c +
-// T_c Z + (S_c^-1 - I) T_c X, where one product u_b = T_b v_b per axis gives
-// X = sum_b S_b^-1 u_b and Z = sum_b (S_b^-1 - I) u_b, and (S_c^-1 - I) T_c X is
-// formed on the layer rows only (an axis without a layer has A = B = 0 and
-// S^-1 = I exactly and skips those terms).  The X and Z terms of every component
-// come first, so X can serve the thin-layer products as scratch.
-int enqueue_delta(const Scpml& s, const float2* v, float2* F, float alpha) {
-  const long long N = s.N;
-  const int* pml = s.p->pml;
-  int rc;
-  for (int b = 0; b < 3; ++b)
-    if ((rc = enqueue_axis_mm(s, b, s.T[b], v + b * N, s.X, 1.0f, b > 0, kMmSplit, s.Z)))
-      return rc;
-  for (int c = 0; c < 3; ++c) {
-    float2* Fc = F + c * N;
-    if ((rc = enqueue_axis_mm(s, c, s.T[c], s.Z, Fc, alpha, false))) return rc;
-    if (pml[c] > 0 && (rc = enqueue_axis_mm(s, c, s.T[c], s.X, Fc, alpha, true, kMmLayer)))
-      return rc;
-  }
-  for (int c = 0; c < 3; ++c) {
-    float2* Fc = F + c * N;
-    const float2* vc = v + c * N;
-    if (pml[c] > 0 && (rc = enqueue_ab(s, c, false, vc, Fc, alpha))) return rc;
-    for (int b = 0; b < 3; ++b)
-      if (b != c && pml[b] > 0 && (rc = enqueue_ab(s, b, true, vc, Fc, alpha))) return rc;
   }
   return CBS_OK;
 }
@@ -2001,6 +1901,45 @@ int enqueue_delta(const Scpml& s, const float2* v, float2* F, float alpha) {
 void gm_grid(long long n, dim3& g) {
   g = dim3((unsigned)std::min<long long>((n + kGmThreads - 1) / kGmThreads, 8192));
 }
+
+// F = alpha (L_s - L) v:  per component c, sum_{b != c} A_b v_c + B_c v_c +
+// T_c Z + (S_c^-1 - I) T_c X with X = sum_b S_b^-1 T_b v_b and Z = sum_b (S_b^-1 -
+// I) T_b v_b.  The first launch of each axis b forms its A_b and B_b terms of
+// every component and u_b = T_b v_b, the second the X and Z terms of component b
+// (an axis without a layer has A = B = 0 and S^-1 = I exactly).
+int enqueue_delta(const Scpml& s, const float2* v, float2* F, float alpha) {
+  cbs_plan_s* p = s.p;
+  ScAxis a;
+  a.v = v;
+  a.F = F;
+  a.u = s.u;
+  for (int b = 0; b < 3; ++b) a.sinv3[b] = s.sinv[b];
+  a.nx = p->nx;
+  a.ny = p->ny;
+  a.nz = p->nz;
+  a.alpha = alpha;
+  const LaunchSc launch[3] = {p->ox->scx, p->oy->scy, p->oz->scz};
+  const float2* tw[3] = {p->twx, p->twy, p->twz};
+  for (int grad = 0; grad < 2; ++grad) {
+    if (grad) {
+      dim3 g;
+      gm_grid(s.N, g);
+      hipLaunchKernelGGL(sc_combine, g, dim3(256), 0, p->stream, a);
+      HIP_LAUNCHED();
+    }
+    for (int b = 0; b < 3; ++b) {
+      a.axis = b;
+      a.first = b == 0 ? 1 : 0;
+      a.p = p->pml[b];
+      a.sinv = s.sinv[b];
+      a.tw = tw[b];
+      launch[b](a, grad != 0, p->stream);
+      HIP_LAUNCHED();
+    }
+  }
+  return CBS_OK;
+}
+
 
 // w = B v = v - (the CBS step from v with the field source -(L_s - L) v):
 // B = gamma [I - G (V - (L_s - L))], the CBS-preconditioned stretched operator

@@ -1008,12 +1008,17 @@ kz_pass(CbsArgs a) {
   }
 }
 
+}  // namespace cbs
+#include "scpml_axis.hpp"
+namespace cbs {
+
 // ---------------------------------------------------------------------------
 // launchers and the per-size registry
 // ---------------------------------------------------------------------------
 using LaunchK1 = void (*)(const CbsArgs&, int mode, hipStream_t);
 using LaunchKY = void (*)(const CbsArgs&, int sign, hipStream_t);
 using LaunchKZ = void (*)(const CbsArgs&, hipStream_t);
+using LaunchSc = void (*)(const ScAxis&, bool grad, hipStream_t);
 
 struct SizeOps {
   int n;
@@ -1021,6 +1026,7 @@ struct SizeOps {
   LaunchK1 k1;        // x axis
   LaunchKY ky;        // y axis
   LaunchKZ kz;        // z axis (nullptr: unsupported on z)
+  LaunchSc scx, scy, scz;   // stretched-layer products along x, y and z (z: nullptr as kz)
   int n1, n2;         // split of the x/y passes (twiddle table layout)
   int z1, z2;         // split of the z pass
   int k1_rows;         // rows per x-pass workgroup when this length is the x axis
@@ -1119,13 +1125,17 @@ constexpr LaunchKZ kxy_for() {
     return nullptr;
 }
 
-#define CBS_SIZE_XYZ(n, a1, a2, z1, z2)                                                  \
-  SizeOps {                                                                              \
-    n, kxy_for<a1, a2>(), &launch_k1<a1, a2>, &launch_ky<a1, a2>, &launch_kz<z1, z2>, a1, a2, z1, z2,       \
-        XGeom<a1, a2>::LINES                                                             \
+#define CBS_SIZE_XYZ(n, a1, a2, z1, z2)                                                         \
+  SizeOps {                                                                                     \
+    n, kxy_for<a1, a2>(), &launch_k1<a1, a2>, &launch_ky<a1, a2>, &launch_kz<z1, z2>,           \
+        &launch_sc<a1, a2, true>, &launch_sc<a1, a2, false>, &launch_sc<z1, z2, false>, a1, a2, \
+        z1, z2, XGeom<a1, a2>::LINES                                                            \
   }
-#define CBS_SIZE_XY(n, a1, a2) \
-  SizeOps { n, nullptr, &launch_k1<a1, a2>, &launch_ky<a1, a2>, nullptr, a1, a2, 0, 0, XGeom<a1, a2>::LINES }
+#define CBS_SIZE_XY(n, a1, a2)                                                           \
+  SizeOps {                                                                              \
+    n, nullptr, &launch_k1<a1, a2>, &launch_ky<a1, a2>, nullptr, &launch_sc<a1, a2, true>, \
+        &launch_sc<a1, a2, false>, nullptr, a1, a2, 0, 0, XGeom<a1, a2>::LINES           \
+  }
 
 // registry, defined in the size translation units
 const SizeOps* find_size(int n);
