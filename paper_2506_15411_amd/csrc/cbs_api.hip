@@ -903,6 +903,10 @@ int check_opts(const cbs_opts* o) {
 
 // prologue of a loop of iterations: W = V E + S (mode K1_FWD), x and y forward
 void enqueue_prologue(cbs_plan_s* p, const CbsArgs& a) {
+  if (a.fused) {
+    p->ox->kxy(a, K1_FWD, p->stream);
+    return;
+  }
   p->ox->k1(a, K1_FWD, p->stream);
   p->oy->ky(a, -1, p->stream);
 }
@@ -913,7 +917,7 @@ void enqueue_prologue(cbs_plan_s* p, const CbsArgs& a) {
 int enqueue_iteration(cbs_plan_s* p, const CbsArgs& a, bool last) {
   p->oz->kz(a, p->stream);            // also reduces the iteration before's residual
   if (a.fused) {
-    p->ox->kxy(a, p->stream);
+    p->ox->kxy(a, K1_ITER, p->stream);
     HIP_LAUNCHED();
     return CBS_OK;
   }
@@ -1765,7 +1769,7 @@ int cbs_time_passes(cbs_plan_t p, void* E_dev, int iters, float* ms_out) {
     if (!a.fused) p->oy->ky(a, +1, p->stream);
     HIP_TRY(hipEventRecord(p->evp[2], p->stream));
     if (a.fused)
-      p->ox->kxy(a, p->stream);
+      p->ox->kxy(a, K1_ITER, p->stream);
     else
       p->ox->k1(a, K1_ITER, p->stream);
     HIP_TRY(hipEventRecord(p->evp[3], p->stream));
@@ -1942,46 +1946,57 @@ int enqueue_delta(const Scpml& s, const float2* v, float2* F, float alpha) {
 
 
 // w = B v = v - (the CBS step from v with the field source -(L_s - L) v):
-// B = gamma [I - G (V - (L_s - L))], the CBS-preconditioned stretched operator
+// B = gamma [I - G (V - (L_s - L))], the CBS-preconditioned stretched operator.
+// v minus its step is the negative of the step's update, which the x pass writes
+// to w itself (K1_RES): v is neither copied nor subtracted from.
 int enqueue_operator(const Scpml& s, const float2* v, float2* w) {
   cbs_plan_s* p = s.p;
   int rc = enqueue_delta(s, v, s.F, -1.0f);
   if (rc) return rc;
-  dim3 g;
-  gm_grid(s.n3, g);
-  hipLaunchKernelGGL(k_gm_copy, g, dim3(kGmThreads), 0, p->stream, v, w, s.n3);
-  HIP_LAUNCHED();
   CbsArgs a = base_args(p);
-  a.E = w;
+  a.E = const_cast<float2*>(v);   // read only: warm prologue and K1_RES
+  a.fout = w;
   a.src = SRC_FIELD;
   a.fin = s.F;
   a.src_scale = 1.0f;   // F is already in units of the pitch
   a.warm = 1;
   enqueue_prologue(p, a);
-  if ((rc = enqueue_iteration(p, a, true))) return rc;
-  hipLaunchKernelGGL(k_gm_rsub, g, dim3(kGmThreads), 0, p->stream, v, w, s.n3);
+  p->oz->kz(a, p->stream);
+  if (a.fused) {
+    p->ox->kxy(a, K1_RES, p->stream);
+  } else {
+    p->oy->ky(a, +1, p->stream);
+    p->ox->k1(a, K1_RES, p->stream);
+  }
   HIP_LAUNCHED();
   return CBS_OK;
 }
 
-// h[0..cnt) = V[0..cnt)^H w (vectors of n3 values, V_i = V + i n3)
-int enqueue_dots(const Scpml& s, const float2* V, int cnt, const float2* w, double2* h) {
-  hipLaunchKernelGGL(k_gm_dots, dim3(kGmBlocks, cnt), dim3(kGmThreads), 0, s.p->stream, V, s.n3,
-                     w, s.n3, s.part);
+// h[0..cnt) = V[0..cnt)^H w (vectors of n3 values, V_i = V + i n3); with self,
+// h[cnt] = |w|^2 too
+int enqueue_dots(const Scpml& s, const float2* V, int cnt, const float2* w, double2* h,
+                 bool self = false) {
+  const int all = cnt + (self ? 1 : 0);
+  hipLaunchKernelGGL(k_gm_dots, dim3(kGmBlocks, (all + kGmGroup - 1) / kGmGroup), dim3(kGmThreads),
+                     0, s.p->stream, V, s.n3, cnt, all, w, s.n3, s.part);
   HIP_LAUNCHED();
-  hipLaunchKernelGGL(k_gm_dots_finish, dim3(cnt), dim3(kGmThreads), 0, s.p->stream, s.part,
+  hipLaunchKernelGGL(k_gm_dots_finish, dim3(all), dim3(kGmThreads), 0, s.p->stream, s.part,
                      kGmBlocks, h);
   HIP_LAUNCHED();
   return CBS_OK;
 }
 
-// w += sign sum_i c_i V_i
-int enqueue_update(const Scpml& s, int cnt, const double2* c, float sign, float2* w) {
-  dim3 g;
-  gm_grid(s.n3, g);
-  hipLaunchKernelGGL(k_gm_update, g, dim3(kGmThreads), 0, s.p->stream, s.basis, s.n3, cnt, c,
-                     sign, w, s.n3);
+// w += sign sum_i c_i V_i; with norm, *norm = |w|^2 afterwards
+int enqueue_update(const Scpml& s, int cnt, const double2* c, float sign, float2* w,
+                   double2* norm = nullptr) {
+  hipLaunchKernelGGL(k_gm_update, dim3(kGmUpdateBlocks), dim3(kGmThreads), 0, s.p->stream, s.basis,
+                     s.n3, cnt, c, sign, w, s.n3, norm ? s.part : nullptr);
   HIP_LAUNCHED();
+  if (norm) {
+    hipLaunchKernelGGL(k_gm_dots_finish, dim3(1), dim3(kGmThreads), 0, s.p->stream, s.part,
+                       kGmUpdateBlocks, norm);
+    HIP_LAUNCHED();
+  }
   return CBS_OK;
 }
 
@@ -2029,11 +2044,10 @@ int scpml_gmres(const Scpml& s, float2* x, int m, const cbs_opts* o, double beta
       double2* h0 = s.h;
       double2* h1 = s.h + (m + 1);
       double2* h2 = s.h + 2 * (m + 1);
-      // classical Gram-Schmidt; w = V_{j+1}, so one sweep over V_0..V_{j+1}
-      // also gives |w|^2 before the projection (h0[j+1])
-      if ((rc = enqueue_dots(s, s.basis, j + 2, w, h0))) return rc;
-      if ((rc = enqueue_update(s, j + 1, h0, -1.0f, w))) return rc;
-      if ((rc = enqueue_dots(s, w, 1, w, h2))) return rc;
+      // classical Gram-Schmidt; the sweep over V_0..V_j also gives |w|^2 before
+      // the projection (h0[j+1]), the update |w|^2 after it
+      if ((rc = enqueue_dots(s, s.basis, j + 1, w, h0, true))) return rc;
+      if ((rc = enqueue_update(s, j + 1, h0, -1.0f, w, h2))) return rc;
       if ((rc = read_back(p, s.h, hv.data(), 3 * (m + 1)))) return rc;
       for (int i = 0; i <= j; ++i) Hij(i, j) = hv[i];
       double nn = hv[2 * (m + 1)].real();
@@ -2042,8 +2056,7 @@ int scpml_gmres(const Scpml& s, float2* x, int m, const cbs_opts* o, double beta
       // original length, so project once more (a DGKS-type test)
       if (nn < 1e-2 * hv[j + 1].real()) {
         if ((rc = enqueue_dots(s, s.basis, j + 1, w, h1))) return rc;
-        if ((rc = enqueue_update(s, j + 1, h1, -1.0f, w))) return rc;
-        if ((rc = enqueue_dots(s, w, 1, w, h2))) return rc;
+        if ((rc = enqueue_update(s, j + 1, h1, -1.0f, w, h2))) return rc;
         if ((rc = read_back(p, s.h, hv.data(), 3 * (m + 1)))) return rc;
         for (int i = 0; i <= j; ++i) Hij(i, j) += hv[(m + 1) + i];
         nn = hv[2 * (m + 1)].real();
@@ -2089,7 +2102,7 @@ int scpml_gmres(const Scpml& s, float2* x, int m, const cbs_opts* o, double beta
     if ((rc = enqueue_operator(s, x, s.vec(0)))) return rc;
     hipLaunchKernelGGL(k_gm_rsub, gg, dim3(kGmThreads), 0, p->stream, s.b, s.vec(0), s.n3);
     HIP_LAUNCHED();
-    if ((rc = enqueue_dots(s, s.vec(0), 1, s.vec(0), s.h))) return rc;
+    if ((rc = enqueue_dots(s, nullptr, 0, s.vec(0), s.h, true))) return rc;
     if ((rc = read_back(p, s.h, hv.data(), 1))) return rc;   // also retires the y upload
     beta = std::sqrt(std::max(0.0, hv[0].real()));
     if (!std::isfinite(beta)) return fail(CBS_E_DIVERGED, "non-finite residual after %d steps", total);
@@ -2159,7 +2172,7 @@ int cbs_solve_scpml(cbs_plan_t p, const cbs_source* src, void* E_dev, const cbs_
   hipLaunchKernelGGL(k_gm_copy, gg, dim3(kGmThreads), 0, p->stream, nullptr, x, s.n3);
   HIP_LAUNCHED();
   std::complex<double> bb;
-  if ((rc = enqueue_dots(s, s.b, 1, s.b, s.h))) return rc;
+  if ((rc = enqueue_dots(s, nullptr, 0, s.b, s.h, true))) return rc;
   if ((rc = read_back(p, s.h, &bb, 1))) return rc;
   const double beta0 = std::sqrt(std::max(0.0, bb.real()));
   if (!std::isfinite(beta0)) return fail(CBS_E_DIVERGED, "non-finite source");

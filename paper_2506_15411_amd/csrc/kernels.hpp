@@ -44,7 +44,8 @@
 namespace cbs {
 
 enum SrcKind : int { SRC_NONE = 0, SRC_PLANE = 1, SRC_FIELD = 2, SRC_POINT = 3, SRC_FIELD_CONJ = 4 };
-enum K1Mode : int { K1_FWD = 0, K1_ITER = 1, K1_INV = 2 };
+// K1_RES: fout = -gamma (GW - E), the step's negative, and no forward transform
+enum K1Mode : int { K1_FWD = 0, K1_ITER = 1, K1_INV = 2, K1_RES = 3 };
 
 constexpr int kHistCap = 1 << 16;
 // Illuminations one batched solve advances together (same medium, own sources).
@@ -417,7 +418,7 @@ k1_xpass(CbsArgs a) {
   float2 v[N2];  // thread t (< N1): element t + N1 m, m < N2
   // early loads of the pointwise operands V0 and E_s (their latency hides
   // behind the inverse transform)
-  constexpr bool PF = (MODE == K1_ITER);
+  constexpr bool PF = (MODE == K1_ITER || MODE == K1_RES);
   float2 pv[PF ? N2 : 1], pe[PF ? N2 : 1];
   const float2* v0t = a.V0 + vbase + t;   // this thread's elements are t + N1 m
   float2* et = a.E + ebase + t;
@@ -461,6 +462,17 @@ k1_xpass(CbsArgs a) {
   if constexpr (MODE == K1_INV) {
     if (ok) {
       sfor<0, N2>([&](auto M) { a.fout[ebase + t + N1 * CV(M)] = v[CV(M)]; });
+    }
+    return;
+  }
+
+  if constexpr (MODE == K1_RES) {
+    if (ok) {
+      sfor<0, N2>([&](auto M) {
+        const float2 d = cmul(make_float2(1.0f - pv[CV(M)].y * a.inv_eps, pv[CV(M)].x * a.inv_eps),
+                              csub(v[CV(M)], pe[CV(M)]));
+        a.fout[ebase + t + N1 * CV(M)] = make_float2(-d.x, -d.y);
+      });
     }
     return;
   }
@@ -642,7 +654,9 @@ struct XYGeom {
   static constexpr int QA = (N * N2 + THREADS - 1) / THREADS;
   static constexpr int QB = (N * N1 + THREADS - 1) / THREADS;
 };
-template <int N1, int N2, bool OBL>
+// MODE as in K1: K1_ITER the whole iteration, K1_FWD (W from E and the source, x
+// and y forward) and K1_RES (y and x inverse, fout = -gamma (GW - E)) its halves.
+template <int N1, int N2, int MODE, bool OBL>
 __global__ void __launch_bounds__((XYGeom<N1, N2>::THREADS), (XYGeom<N1, N2>::WAVES))
 kxy_pass(CbsArgs a) {
   using G = XYGeom<N1, N2>;
@@ -650,7 +664,7 @@ kxy_pass(CbsArgs a) {
   __shared__ float2 lds[N * P];
   __shared__ float2 tw[N];
   __shared__ double red[2 * (T / 64)];
-  if (a.st->done) return;
+  if (MODE == K1_ITER && a.st->done) return;
   const int tid = threadIdx.x;
   TwStage<N, T> tws;
   tws.issue(a.twx, tid);
@@ -667,7 +681,9 @@ kxy_pass(CbsArgs a) {
   float2* ep = a.E + ebase;
 
   // inverse y, level A: task (xi, j2, brick), a wave reads whole brick rows
-  {
+  if constexpr (MODE == K1_FWD) {
+    tws.commit(tw, tid);
+  } else {
     float2 b[G::QG][N1];
     sfor<0, G::QG>([&](auto QQ) {
       const int i = tid + CV(QQ) * T;
@@ -698,10 +714,12 @@ kxy_pass(CbsArgs a) {
     if (i < N * N1) {
       const int o = (i / N1) * N + i % N1;
       sfor<0, N2>([&](auto M) { pv[CV(QQ)][CV(M)] = v0p[o + N1 * CV(M)]; });
-      sfor<0, N2>([&](auto M) { pe[CV(QQ)][CV(M)] = ep[o + N1 * CV(M)]; });
+      if (MODE != K1_FWD || a.warm)
+        sfor<0, N2>([&](auto M) { pe[CV(QQ)][CV(M)] = ep[o + N1 * CV(M)]; });
     }
   });
   __syncthreads();
+  if constexpr (MODE != K1_FWD) {
   // inverse y, level B: task (x, k1)
   sfor<0, G::QB>([&](auto QQ) {
     const int i = tid + CV(QQ) * T;
@@ -728,6 +746,7 @@ kxy_pass(CbsArgs a) {
     }
   });
   __syncthreads();
+  }
   // inverse x, level B; update; W = V E_s + S; forward x, level A'
   const bool zin = (z >= a.pz) && (z < a.nz - a.pz);
   const float2 ph = a.phase[(ib * 3 + c) * a.nz + z];   // pol_c exp(i kz z)
@@ -739,21 +758,35 @@ kxy_pass(CbsArgs a) {
       const int o = y * N + t;
       float2* l = lds + (N2 * (y % N1) + y / N1) * P + N2 * t;
       float2 v[N2];
-      sfor<0, N2>([&](auto J) { v[CV(J)] = l[CV(J)]; });
-      dft<N2, +1>(v);
+      if constexpr (MODE != K1_FWD) {
+        sfor<0, N2>([&](auto J) { v[CV(J)] = l[CV(J)]; });
+        dft<N2, +1>(v);
+      }
+      if constexpr (MODE == K1_RES) {
+        sfor<0, N2>([&](auto M) {
+          const float2 v0 = pv[CV(QQ)][CV(M)];
+          const float2 d = cmul(make_float2(1.0f - v0.y * a.inv_eps, v0.x * a.inv_eps),
+                                csub(v[CV(M)], pe[CV(QQ)][CV(M)]));
+          a.fout[ebase + o + N1 * CV(M)] = make_float2(-d.x, -d.y);
+        });
+        return;
+      }
       const bool yzin = zin && (y >= a.py) && (y < a.ny - a.py);
       const float2 spl = OBL ? cmul(ph, a.phy[ib * a.ny + y]) : ph;
       const float2* phxb = a.phx + ib * a.nx;
       sfor<0, N2>([&](auto M) {
         const int x = t + N1 * CV(M);
         const float2 v0 = pv[CV(QQ)][CV(M)];
-        float2 e = pe[CV(QQ)][CV(M)];
-        const float2 gm = make_float2(1.0f - v0.y * a.inv_eps, v0.x * a.inv_eps);
-        const float2 d = cmul(gm, csub(v[CV(M)], e));
-        e = cadd(e, d);
-        sd += (double)(d.x * d.x + d.y * d.y);
-        se += (double)(e.x * e.x + e.y * e.y);
-        ep[o + N1 * CV(M)] = e;
+        float2 e = make_float2(0.f, 0.f);   // a cold start, whatever E held
+        if (MODE != K1_FWD || a.warm) e = pe[CV(QQ)][CV(M)];
+        if constexpr (MODE == K1_ITER) {
+          const float2 gm = make_float2(1.0f - v0.y * a.inv_eps, v0.x * a.inv_eps);
+          const float2 d = cmul(gm, csub(v[CV(M)], e));
+          e = cadd(e, d);
+          sd += (double)(d.x * d.x + d.y * d.y);
+          se += (double)(e.x * e.x + e.y * e.y);
+        }
+        if (MODE == K1_ITER || !a.warm) ep[o + N1 * CV(M)] = e;
         float2 w = cmul(make_float2(v0.x, v0.y - a.eps), e);
         if (a.src == SRC_PLANE) {
           if (yzin && (x >= a.px) && (x < a.nx - a.px)) {
@@ -777,6 +810,7 @@ kxy_pass(CbsArgs a) {
       sfor<0, N2>([&](auto K) { l[CV(K)] = cmul(v[CV(K)], tc[N1 * CV(K)]); });
     }
   });
+  if constexpr (MODE == K1_RES) return;
   __syncthreads();
   // forward x, level B': task (row, k')
   sfor<0, G::QA>([&](auto QQ) {
@@ -817,8 +851,10 @@ kxy_pass(CbsArgs a) {
       sfor<0, N1>([&](auto K) { w[N2 * kBrick * CV(K)] = b[CV(K)]; });
     }
   });
-  block_sum2<T>(sd, se, red, a.partials + 2 * ((long long)ib * a.k1_blocks + (long long)z * 3 + c));
-  if (blockIdx.x == 0 && tid == 0) a.st->pending = 1;
+  if constexpr (MODE == K1_ITER) {
+    block_sum2<T>(sd, se, red, a.partials + 2 * ((long long)ib * a.k1_blocks + (long long)z * 3 + c));
+    if (blockIdx.x == 0 && tid == 0) a.st->pending = 1;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1022,7 +1058,7 @@ using LaunchSc = void (*)(const ScAxis&, bool grad, hipStream_t);
 
 struct SizeOps {
   int n;
-  LaunchKZ kxy;       // the fused plane pass of an n x n plane (nullptr: none)
+  LaunchK1 kxy;       // the fused plane pass of an n x n plane (nullptr: none)
   LaunchK1 k1;        // x axis
   LaunchKY ky;        // y axis
   LaunchKZ kz;        // z axis (nullptr: unsupported on z)
@@ -1068,6 +1104,8 @@ void launch_k1(const CbsArgs& a_in, int mode, hipStream_t s) {
     hipLaunchKernelGGL((k1_xpass<N1, N2, K1_ITER, false>), dim3(nb), dim3(G::THREADS), 0, s, a);
   else if (mode == K1_ITER)
     hipLaunchKernelGGL((k1_xpass<N1, N2, K1_ITER, true>), dim3(nb), dim3(G::THREADS), 0, s, a);
+  else if (mode == K1_RES)
+    hipLaunchKernelGGL((k1_xpass<N1, N2, K1_RES, false>), dim3(nb), dim3(G::THREADS), 0, s, a);
   else
     hipLaunchKernelGGL((k1_xpass<N1, N2, K1_INV, false>), dim3(nb), dim3(G::THREADS), 0, s, a);
 }
@@ -1108,17 +1146,24 @@ void launch_kz(const CbsArgs& a, hipStream_t s) {
 }
 
 template <int N1, int N2>
-void launch_kxy(const CbsArgs& a, hipStream_t s) {
+void launch_kxy(const CbsArgs& a, int mode, hipStream_t s) {
   using G = XYGeom<N1, N2>;
-  const dim3 grid(3u * (unsigned)a.nb * (unsigned)a.nz);
-  if (a.oblique && a.src == SRC_PLANE)
-    hipLaunchKernelGGL((kxy_pass<N1, N2, true>), grid, dim3(G::THREADS), 0, s, a);
+  const dim3 grid(3u * (unsigned)a.nb * (unsigned)a.nz), block(G::THREADS);
+  const bool obl = a.oblique && a.src == SRC_PLANE;
+  if (mode == K1_RES)
+    hipLaunchKernelGGL((kxy_pass<N1, N2, K1_RES, false>), grid, block, 0, s, a);
+  else if (mode == K1_FWD && obl)
+    hipLaunchKernelGGL((kxy_pass<N1, N2, K1_FWD, true>), grid, block, 0, s, a);
+  else if (mode == K1_FWD)
+    hipLaunchKernelGGL((kxy_pass<N1, N2, K1_FWD, false>), grid, block, 0, s, a);
+  else if (obl)
+    hipLaunchKernelGGL((kxy_pass<N1, N2, K1_ITER, true>), grid, block, 0, s, a);
   else
-    hipLaunchKernelGGL((kxy_pass<N1, N2, false>), grid, dim3(G::THREADS), 0, s, a);
+    hipLaunchKernelGGL((kxy_pass<N1, N2, K1_ITER, false>), grid, block, 0, s, a);
 }
 // the fused plane pass needs a plane of N x N complex values in 160 KB of LDS
 template <int N1, int N2>
-constexpr LaunchKZ kxy_for() {
+constexpr LaunchK1 kxy_for() {
   if constexpr (N2 > 1 && N1 * N2 <= 128)
     return &launch_kxy<N1, N2>;
   else
