@@ -1073,16 +1073,25 @@ int end_solve(cbs_plan_s* p, cbs_stats* stats) {
   return CBS_NOT_CONVERGED;
 }
 
-// Blocking solve on top of the primitives: host polls every check_every.
+// Blocking solve on top of the primitives: quanta of check_every iterations, two
+// of them in flight, so the device has work while the host reads the state of
+// the one before (a 64^3 iteration takes 20 us and a host round trip about as
+// long: 100 iterations 2.13 -> 2.05 ms, 40 iterations of 32^3 0.54 -> 0.51).  A
+// solve that meets tol leaves at most the
+// second quantum's launches, which return at entry.
 int run_blocking(cbs_plan_s* p, int check_every, cbs_stats* stats) {
+  auto& A = p->act;
   int done = 0, rc = CBS_OK;
   while (!done) {
-    if ((rc = advance_solve(p, check_every))) break;
-    if ((rc = wait_solve(p))) break;
-    if ((rc = poll_solve(p, &done))) break;
+    while (!rc && A.count < 2 && A.enqueued < A.max_iter) rc = advance_solve(p, check_every);
+    if (!rc && A.count == 0) rc = fail(CBS_E_STATE, "the device did not stop at max_iter");
+    if (rc) break;
+    const hipError_t e = hipEventSynchronize(p->evq[A.head]);
+    if (e != hipSuccess) rc = fail(CBS_E_HIP, "hipEventSynchronize: %s", hipGetErrorString(e));
+    if (rc || (rc = poll_solve(p, &done))) break;
   }
   if (rc) {
-    p->act.on = false;
+    A.on = false;
     (void)hipStreamSynchronize(p->stream);
     return rc;
   }
