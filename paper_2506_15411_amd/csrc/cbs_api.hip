@@ -275,7 +275,7 @@ __global__ void k_gradient(const float2* E, const float2* Ea, long long sE, int 
 // ---------------------------------------------------------------------------
 // lens metrics: focus search, line profiles, disc power (FP64 reductions)
 // ---------------------------------------------------------------------------
-constexpr int kMetricBlocks = 256;
+constexpr int kMetricBlocks = 1024;
 constexpr int kMetricThreads = 256;
 
 __device__ __forceinline__ double intensity(const float2* E, long long sE, long long idx) {
@@ -297,13 +297,10 @@ k_argmax_intensity(const float2* E, long long sE, int nx, int ny, int x0, int y0
   __shared__ long long si[kMetricThreads];
   double best = -1.0;
   long long bi = 0x7fffffffffffffffLL;
-  const long long NB = (long long)bx * by * bz;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < NB;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int xi = (int)(i % bx);
-    const long long r = i / bx;
-    const int yi = (int)(r % by);
-    const int zi = (int)(r / by);
+  const unsigned NB = (unsigned)bx * by * bz;   // a grid holds fewer than 2^31 voxels
+  for (unsigned i = blockIdx.x * kMetricThreads + threadIdx.x; i < NB; i += gridDim.x * kMetricThreads) {
+    const unsigned r = i / (unsigned)bx, xi = i - r * bx;
+    const unsigned zi = r / (unsigned)by, yi = r - zi * by;
     const long long idx = ((long long)(z0 + zi) * ny + (y0 + yi)) * nx + (x0 + xi);
     const double s = intensity(E, sE, idx);
     if (s > best || (s == best && idx < bi)) {
@@ -331,10 +328,36 @@ k_argmax_intensity(const float2* E, long long sE, int nx, int ny, int x0, int y0
   }
 }
 
-// |E|^2 along the x, y and z lines through (fx, fy, fz): out[0, nx) then
+// The maximum of the per-block maxima of k_argmax_intensity (same tie rule):
+// focus[0] = |E|^2, focus[1] = linear voxel index.  One work-group, one wave.
+__global__ void k_argmax_finish(const double* part, int nb, double* focus) {
+  double best = -1.0, bi = 1e300;
+  for (int b = threadIdx.x; b < nb; b += 64) {
+    const double v = part[2 * b], j = part[2 * b + 1];
+    if (v > best || (v == best && j < bi)) {
+      best = v;
+      bi = j;
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    const double v = __shfl_xor(best, o, 64), j = __shfl_xor(bi, o, 64);
+    if (v > best || (v == best && j < bi)) {
+      best = v;
+      bi = j;
+    }
+  }
+  if (threadIdx.x == 0) {   // no finite |E|^2 in the box: -1 at voxel 0
+    focus[0] = best;
+    focus[1] = best < 0.0 ? 0.0 : bi;
+  }
+}
+
+// |E|^2 along the x, y and z lines through the focus: out[0, nx) then
 // out[nx, nx + ny) then out[nx + ny, nx + ny + nz).
-__global__ void k_line_intensity(const float2* E, long long sE, int nx, int ny, int nz, int fx,
-                                 int fy, int fz, double* out) {
+__global__ void k_line_intensity(const float2* E, long long sE, int nx, int ny, int nz,
+                                 const double* focus, double* out) {
+  const long long bi = (long long)focus[1];
+  const int fx = (int)(bi % nx), fy = (int)((bi / nx) % ny), fz = (int)(bi / ((long long)nx * ny));
   const int n = nx + ny + nz;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     int x = fx, y = fy, z = fz;
@@ -345,39 +368,74 @@ __global__ void k_line_intensity(const float2* E, long long sE, int nx, int ny, 
   }
 }
 
-// The transverse field of plane fz in FP64: ex, ey [ny][nx].
-__global__ void k_plane_extract(const float2* E, long long sE, int nx, int ny, int fz,
-                                double2* ex, double2* ey) {
+// The transverse field of the focal plane in FP64: ex, ey [ny][nx].
+__global__ void k_plane_extract(const float2* E, long long sE, int nx, int ny,
+                                const double* focus, double2* ex, double2* ey) {
   const long long NP = (long long)nx * ny;
+  const long long fz = (long long)focus[1] / NP;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < NP;
        i += (long long)gridDim.x * blockDim.x) {
-    const float2 a = E[(long long)fz * NP + i], b = E[sE + (long long)fz * NP + i];
+    const float2 a = E[fz * NP + i], b = E[sE + fz * NP + i];
     ex[i] = make_double2(a.x, a.y);
     ey[i] = make_double2(b.x, b.y);
   }
 }
 
-// One pass of a plane DFT in FP64, out-of-place: along x (axis 0) or y
-// (axis 1) of an [ny][nx] plane, out[k] = sum_j in[j] w^(sign j k), with
-// w = tw[m] = exp(-2 pi i m / n) (sign -1: forward, +1: inverse, unscaled).
-// Direct sums: the planes are small and this runs once per measurement.
-__global__ void k_plane_dft(const double2* in, double2* out, int nx, int ny, int axis, int sign,
-                            const double2* tw) {
-  const long long NP = (long long)nx * ny;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < NP;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int x = (int)(i % nx), y = (int)(i / nx);
-    const int n = axis == 0 ? nx : ny;
-    const int k = axis == 0 ? x : y;
-    double re = 0.0, im = 0.0;
-    for (int j = 0; j < n; ++j) {
-      const double2 v = axis == 0 ? in[(long long)y * nx + j] : in[(long long)j * nx + x];
-      const double2 w = tw[(int)(((long long)j * k) % n)];
-      const double wi = sign < 0 ? w.y : -w.y;
-      re += v.x * w.x - v.y * wi;
-      im += v.x * wi + v.y * w.x;
+// One pass of plane DFTs in FP64, in place: the lines of the [ny][nx] planes that
+// follow each other (blockIdx.y), along x (axis 0) or y (axis 1), out[k] = sum_j
+// in[j] w^(sign j k), w = tw[m] = exp(-2 pi i m / n) (sign -1: forward, +1:
+// inverse, unscaled).  A work-group holds kDftLines lines and the table in LDS;
+// n = n1 n2 is summed in the two levels of the passes, n1 + n2 terms an output
+// (direct sums of n terms from global memory took 84 us a 275 x 275 plane and
+// axis, from LDS for four planes at once 42; now 14 for the four).
+constexpr int kDftLines = 2;
+constexpr int kDftThreads = 512;
+__global__ void __launch_bounds__(kDftThreads)
+k_plane_dft(double2* planes, int nx, int ny, int axis, int sign, int n1, int n2,
+            const double2* tw) {
+  extern __shared__ double2 sh[];   // lines, their level-A results, the table
+  const int n = axis == 0 ? nx : ny, lines = axis == 0 ? ny : nx;
+  const long long ls = axis == 0 ? nx : 1, es = axis == 0 ? 1 : nx;
+  const int l0 = blockIdx.x * kDftLines, tasks = kDftLines * n;
+  double2* f = planes + (long long)blockIdx.y * nx * ny + l0 * ls;
+  double2 *mid = sh + tasks, *t = mid + tasks;
+  for (int i = threadIdx.x; i < tasks; i += kDftThreads) {
+    // consecutive threads along the contiguous direction
+    const int r = axis == 0 ? i / n : i % kDftLines, j = axis == 0 ? i % n : i / kDftLines;
+    sh[r * n + j] = l0 + r < lines ? f[r * ls + j * es] : make_double2(0.0, 0.0);
+  }
+  for (int i = threadIdx.x; i < n; i += kDftThreads) {
+    const double2 w = tw[i];
+    t[i] = make_double2(w.x, sign < 0 ? w.y : -w.y);
+  }
+  __syncthreads();
+  // level A: mid[j2 n1 + k1] = w^(j2 k1) sum_j1 in[j2 + n2 j1] w^(n2 j1 k1)
+  for (int i = threadIdx.x; i < tasks; i += kDftThreads) {
+    const int r = i / n, q = i - r * n, j2 = q / n1, k1 = q - j2 * n1;
+    const double2* v = sh + r * n + j2;
+    double2 s = make_double2(0.0, 0.0);
+    int m = 0;   // j1 k1 mod n1
+    for (int j1 = 0; j1 < n1; ++j1) {
+      s = zadd(s, zmul(v[n2 * j1], t[m * n2]));
+      m += k1;
+      m -= m >= n1 ? n1 : 0;
     }
-    out[i] = make_double2(re, im);
+    mid[i] = zmul(s, t[j2 * k1]);
+  }
+  __syncthreads();
+  // level B: out[k1 + n1 k2] = sum_j2 mid[j2 n1 + k1] w^(n1 j2 k2)
+  for (int i = threadIdx.x; i < tasks; i += kDftThreads) {
+    const int r = axis == 0 ? i / n : i % kDftLines, k = axis == 0 ? i - r * n : i / kDftLines;
+    const int k2 = k / n1, k1 = k - k2 * n1;
+    const double2* v = mid + r * n + k1;
+    double2 s = make_double2(0.0, 0.0);
+    int m = 0;   // j2 k2 mod n2
+    for (int j2 = 0; j2 < n2; ++j2) {
+      s = zadd(s, zmul(v[j2 * n1], t[m * n1]));
+      m += k2;
+      m -= m >= n2 ? n2 : 0;
+    }
+    if (l0 + r < lines) f[r * ls + k * es] = s;
   }
 }
 
@@ -674,8 +732,8 @@ bool layout_of(int nx, int ny, int nz, Layout& L) {
   L.partials = take((size_t)2 * k1b * sizeof(double));
   L.setup = take((size_t)2 * kSetupBlocks * sizeof(double));
   L.hist = take((size_t)kHistCap * sizeof(double));
-  L.metrics = take((size_t)(2 * kMetricBlocks + nx + ny + nz + 1) * sizeof(double) +
-                   (size_t)(nx + ny + 5 * N / nz) * sizeof(double2));
+  L.metrics = take((size_t)(2 * kMetricBlocks + 2 + nx + ny + nz + 1) * sizeof(double) +
+                   (size_t)(nx + ny + 4 * N / nz) * sizeof(double2));
   L.state = take(sizeof(DevState));
   L.total = off;
   return true;
@@ -1590,80 +1648,78 @@ int cbs_lens_metrics(cbs_plan_t p, const void* E, const int lo[3], const int hi[
   const int bx = hi[0] - lo[0], by = hi[1] - lo[1], bz = hi[2] - lo[2];
   const long long NB = (long long)bx * by * bz;
   const int nb = (int)std::min<long long>(kMetricBlocks, (NB + kMetricThreads - 1) / kMetricThreads);
-  // 1. focus: the maximum of |E|^2 in the box
-  hipLaunchKernelGGL(k_argmax_intensity, dim3(nb), dim3(kMetricThreads), 0, p->stream, F, sE,
-                     p->nx, p->ny, lo[0], lo[1], lo[2], bx, by, bz, p->metrics);
+  // 1. focus: the maximum of |E|^2 in the box, 2. the profiles through it, and
+  // the spectral fields of its plane; the host waits once for focus and profiles
+  const int nx = p->nx, ny = p->ny;
+  const long long NP = (long long)nx * ny;
+  const int nl = nx + ny + p->nz;
+  double* focus = p->metrics + 2 * kMetricBlocks;   // 2 values, then the profiles
+  double* lines = focus + 2;
+  double2* twx = reinterpret_cast<double2*>(lines + ((nl + 1) & ~1));   // 16-byte aligned
+  double2* twy = twx + nx;
+  double2* pl = twy + ny;   // 4 planes
+  hipLaunchKernelGGL(k_argmax_intensity, dim3(nb), dim3(kMetricThreads), 0, p->stream, F, sE, nx, ny,
+                     lo[0], lo[1], lo[2], bx, by, bz, p->metrics);
   HIP_LAUNCHED();
-  std::vector<double> part(2 * kMetricBlocks);
-  HIP_TRY(hipMemcpyAsync(part.data(), p->metrics, 2 * nb * sizeof(double), hipMemcpyDeviceToHost,
+  hipLaunchKernelGGL(k_argmax_finish, dim3(1), dim3(64), 0, p->stream, p->metrics, nb, focus);
+  HIP_LAUNCHED();
+  hipLaunchKernelGGL(k_line_intensity, dim3((nl + 255) / 256), dim3(256), 0, p->stream, F, sE, nx, ny,
+                     p->nz, focus, lines);
+  HIP_LAUNCHED();
+  std::vector<double> prof(nl + 2);
+  HIP_TRY(hipMemcpyAsync(prof.data(), focus, (nl + 2) * sizeof(double), hipMemcpyDeviceToHost,
                          p->stream));
   HIP_TRY(hipStreamSynchronize(p->stream));
-  double best = -1.0;
-  long long bi = 0;
-  for (int b = 0; b < nb; ++b)
-    if (part[2 * b] > best || (part[2 * b] == best && (long long)part[2 * b + 1] < bi)) {
-      best = part[2 * b];
-      bi = (long long)part[2 * b + 1];
-    }
-  const int fx = (int)(bi % p->nx), fy = (int)((bi / p->nx) % p->ny), fz = (int)(bi / ((long long)p->nx * p->ny));
-  // 2. profiles through the focus and their widths
-  const int nl = p->nx + p->ny + p->nz;
-  double* lines = p->metrics + 2 * kMetricBlocks;
-  hipLaunchKernelGGL(k_line_intensity, dim3((nl + 255) / 256), dim3(256), 0, p->stream, F, sE,
-                     p->nx, p->ny, p->nz, fx, fy, fz, lines);
-  HIP_LAUNCHED();
-  std::vector<double> prof(nl);
-  HIP_TRY(hipMemcpyAsync(prof.data(), lines, nl * sizeof(double), hipMemcpyDeviceToHost, p->stream));
-  HIP_TRY(hipStreamSynchronize(p->stream));
+  const double* lp = prof.data() + 2;
+  const double best = prof[0];
+  const long long bi = (long long)prof[1];
+  const int fx = (int)(bi % nx), fy = (int)((bi / nx) % ny), fz = (int)(bi / NP);
   out->focus[0] = fx;
   out->focus[1] = fy;
   out->focus[2] = fz;
   out->peak = best;
-  out->fwhm[0] = fwhm_of(prof.data(), p->nx, fx, p->pitch);
-  out->fwhm[1] = fwhm_of(prof.data() + p->nx, p->ny, fy, p->pitch);
-  out->fwhm[2] = fwhm_of(prof.data() + p->nx + p->ny, p->nz, fz, p->pitch);
+  out->fwhm[0] = fwhm_of(lp, nx, fx, p->pitch);
+  out->fwhm[1] = fwhm_of(lp + nx, ny, fy, p->pitch);
+  out->fwhm[2] = fwhm_of(lp + nx + ny, p->nz, fz, p->pitch);
   // 3. power through the disc of diameter disc_factor x lateral FWHM: the
   // Poynting flux of the plane's propagating angular spectrum
   out->disc_flux = std::nan("");
   out->eta_f = std::nan("");
   if (std::isfinite(out->fwhm[0]) && std::isfinite(out->fwhm[1])) {
-    const int nx = p->nx, ny = p->ny;
-    const long long NP = (long long)nx * ny;
-    double2* twx = reinterpret_cast<double2*>(lines + ((nl + 1) & ~1));   // 16-byte aligned
-    double2* twy = twx + nx;
-    double2* pl[5];
-    for (int k = 0; k < 5; ++k) pl[k] = twy + ny + k * NP;
     std::vector<double2> t(nx + ny);
     for (int m = 0; m < nx; ++m) t[m] = make_double2(std::cos(2 * M_PI * m / nx), -std::sin(2 * M_PI * m / nx));
     for (int m = 0; m < ny; ++m) t[nx + m] = make_double2(std::cos(2 * M_PI * m / ny), -std::sin(2 * M_PI * m / ny));
     HIP_TRY(hipMemcpyAsync(twx, t.data(), (nx + ny) * sizeof(double2), hipMemcpyHostToDevice, p->stream));
     const dim3 g((unsigned)std::min<long long>(4096, (NP + 255) / 256)), b(256);
-    // pl[0] = Ex, pl[1] = Ey, pl[4] scratch; forward 2D DFTs in place via scratch
-    hipLaunchKernelGGL(k_plane_extract, g, b, 0, p->stream, F, sE, nx, ny, fz, pl[0], pl[1]);
+    hipLaunchKernelGGL(k_plane_extract, g, b, 0, p->stream, F, sE, nx, ny, focus, pl, pl + NP);
     HIP_LAUNCHED();
-    auto dft2 = [&](double2* f, int sign) -> int {
-      hipLaunchKernelGGL(k_plane_dft, g, b, 0, p->stream, f, pl[4], nx, ny, 0, sign, twx);
-      HIP_LAUNCHED();
-      hipLaunchKernelGGL(k_plane_dft, g, b, 0, p->stream, pl[4], f, nx, ny, 1, sign, twy);
-      HIP_LAUNCHED();
+    // 2D DFTs of the first `fields` planes in place
+    auto dft2 = [&](int fields, int sign) -> int {
+      for (int axis = 0; axis < 2; ++axis) {
+        const SizeOps* o = axis == 0 ? p->ox : p->oy;
+        const int n = axis == 0 ? nx : ny, ln = axis == 0 ? ny : nx;
+        hipLaunchKernelGGL(k_plane_dft, dim3((ln + kDftLines - 1) / kDftLines, fields),
+                           dim3(kDftThreads), (size_t)(2 * kDftLines + 1) * n * sizeof(double2),
+                           p->stream, pl, nx, ny, axis, sign, o->n1, o->n2, axis == 0 ? twx : twy);
+        HIP_LAUNCHED();
+      }
       return CBS_OK;
     };
-    if ((rc = dft2(pl[0], -1)) || (rc = dft2(pl[1], -1))) return rc;
+    if ((rc = dft2(2, -1))) return rc;
     const double k = 2.0 * M_PI * p->n_bg / p->lambda0;
-    hipLaunchKernelGGL(k_angular_h, g, b, 0, p->stream, pl[0], pl[1], pl[2], pl[3], nx, ny,
+    hipLaunchKernelGGL(k_angular_h, g, b, 0, p->stream, pl, pl + NP, pl + 2 * NP, pl + 3 * NP, nx, ny,
                        2.0 * M_PI / (nx * p->pitch), 2.0 * M_PI / (ny * p->pitch), k);
     HIP_LAUNCHED();
-    for (int q = 0; q < 4; ++q)
-      if ((rc = dft2(pl[q], +1))) return rc;
+    if ((rc = dft2(4, +1))) return rc;
     const double radius = 0.5 * disc_factor * 0.5 * (out->fwhm[0] + out->fwhm[1]) / p->pitch;
-    const int nd = (int)std::min<long long>(kMetricBlocks, (NP + kMetricThreads - 1) / kMetricThreads);
+    const int nd = (int)std::min<long long>(256, (NP + kMetricThreads - 1) / kMetricThreads);
     const double scale = 1.0 / ((double)NP * (double)NP);   // two unscaled inverse transforms
-    hipLaunchKernelGGL(k_disc_flux, dim3(nd), dim3(kMetricThreads), 0, p->stream, pl[0], pl[1],
-                       pl[2], pl[3], nx, ny, (double)fx, (double)fy, radius * radius, scale,
+    hipLaunchKernelGGL(k_disc_flux, dim3(nd), dim3(kMetricThreads), 0, p->stream, pl, pl + NP,
+                       pl + 2 * NP, pl + 3 * NP, nx, ny, (double)fx, (double)fy, radius * radius, scale,
                        p->metrics);
     HIP_LAUNCHED();
-    HIP_TRY(hipMemcpyAsync(part.data(), p->metrics, nd * sizeof(double), hipMemcpyDeviceToHost,
-                           p->stream));
+    double part[256];
+    HIP_TRY(hipMemcpyAsync(part, p->metrics, nd * sizeof(double), hipMemcpyDeviceToHost, p->stream));
     HIP_TRY(hipStreamSynchronize(p->stream));
     double sum = 0.0;
     for (int q = 0; q < nd; ++q) sum += part[q];
