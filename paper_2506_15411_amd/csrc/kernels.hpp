@@ -231,8 +231,8 @@ constexpr int round64(int t) { return (t + 63) / 64 * 64; }
 // group then leaves part of the CU empty.  Measured on these splits, x pass in
 // us (rows: time):
 // 189 = 27 x 7: 4: 99, 5: 110, 6: 96, 7: 87, 8: 96; 315 = 35 x 9: 3: 262, 5: 241,
-// 7: 226, 8: 478; 275 = 25 x 11: 4: 574, 5: 537, 7: 576; 261 = 29 x 9 (177
-// registers): 4: 207, 7: 235; 621 = 27 x 23 (197): 4: 605, 7: 640, 8: 627.
+// 7: 226, 8: 478; 275 = 25 x 11: 4: 574, 5: 537, 7: 576; 261 = 29 x 9:
+// 4: 166, 7: 175; 621 = 27 x 23 (198 registers): 4: 605, 7: 640, 8: 627.
 constexpr int codelet_ops(int n) {
   int ops = 0, m = n;
   for (int p = 2; m > 1; ++p)
@@ -416,18 +416,14 @@ k1_xpass(CbsArgs a) {
   const long long vbase = ((long long)z * a.ny + y) * a.nx;             // V0 row
 
   float2 v[N2];  // thread t (< N1): element t + N1 m, m < N2
-  // early loads of the pointwise operands V0 and E_s (their latency hides
-  // behind the inverse transform)
+  // the pointwise operands V0 and E_s, loaded between the levels of the inverse
+  // transform: their latency hides behind the second, and the first does not
+  // hold their registers (before it: 261 points 177 registers and 208 us, now
+  // 168 us; 256 158 -> 150, 189 78 -> 73, 315 223 -> 214, 275 and 621 unchanged)
   constexpr bool PF = (MODE == K1_ITER || MODE == K1_RES);
   float2 pv[PF ? N2 : 1], pe[PF ? N2 : 1];
   const float2* v0t = a.V0 + vbase + t;   // this thread's elements are t + N1 m
   float2* et = a.E + ebase + t;
-  if constexpr (PF) {
-    if (ok) {
-      sfor<0, N2>([&](auto M) { pv[CV(M)] = v0t[N1 * CV(M)]; });
-      sfor<0, N2>([&](auto M) { pe[CV(M)] = et[N1 * CV(M)]; });
-    }
-  }
 
   // element x of this thread's row in the bricks
   float2* wrow = wb + la * kBrick;
@@ -450,6 +446,12 @@ k1_xpass(CbsArgs a) {
       sfor<0, N1>([&](auto K1) { b[CV(K1)] = cmulc(b[CV(K1)], twt[CV(K1)]); });
       sfor<0, N1>([&](auto K1) { La[ta + N2 * CV(K1)] = b[CV(K1)]; });
     }
+  if constexpr (PF) {
+    if (ok) {
+      sfor<0, N2>([&](auto M) { pv[CV(M)] = v0t[N1 * CV(M)]; });
+      sfor<0, N2>([&](auto M) { pe[CV(M)] = et[N1 * CV(M)]; });
+    }
+  }
     __syncthreads();
     // inverse level B: thread k1 = t < N1, DFT-N2 over Lr[N2 k1 + j2]
     if (ok) {
