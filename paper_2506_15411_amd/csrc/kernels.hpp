@@ -44,6 +44,13 @@
 namespace cbs {
 
 enum SrcKind : int { SRC_NONE = 0, SRC_PLANE = 1, SRC_FIELD = 2, SRC_POINT = 3, SRC_FIELD_CONJ = 4 };
+// Source forms the x and plane passes are compiled for (the launchers choose):
+// plane waves at normal incidence, points and none; an oblique illumination among
+// the plane waves (a per-element x phase); a field, loaded with the other
+// pointwise operands (in the update loop its loads waited one by one behind the
+// stores of E_s: x pass of 192 x 192 x 256 239 us, now 228; prologue of 275 x 275
+// x 315 470, now 386).
+enum SrcForm : int { FORM_PLAIN = 0, FORM_OBLIQUE = 1, FORM_FIELD = 2 };
 // K1_RES: fout = -gamma (GW - E), the step's negative, and no forward transform
 enum K1Mode : int { K1_FWD = 0, K1_ITER = 1, K1_INV = 2, K1_RES = 3 };
 
@@ -367,9 +374,7 @@ __device__ __forceinline__ void block_sum2(double a, double b, double* red, doub
 // sits at brick x/8, offset 8 y + x%8, so the R rows of one brick form one
 // contiguous 64 R-byte piece.  The inverse transform, the update and the
 // forward transform share one LDS exchange buffer per row.
-// OBL: some illumination is oblique, so the plane-wave source carries a per-
-// element x phase (a separate instantiation keeps it out of the normal path)
-template <int N1, int N2, int MODE, bool OBL>
+template <int N1, int N2, int MODE, int FORM>
 __global__ void __launch_bounds__((XGeom<N1, N2>::THREADS))
 k1_xpass(CbsArgs a) {
   using G = XGeom<N1, N2>;
@@ -420,10 +425,23 @@ k1_xpass(CbsArgs a) {
   // transform: their latency hides behind the second, and the first does not
   // hold their registers (before it: 261 points 177 registers and 208 us, now
   // 168 us; 256 158 -> 150, 189 78 -> 73, 315 223 -> 214, 275 and 621 unchanged)
-  constexpr bool PF = (MODE == K1_ITER || MODE == K1_RES);
-  float2 pv[PF ? N2 : 1], pe[PF ? N2 : 1];
+  constexpr bool PF = MODE != K1_INV;
+  constexpr bool FIELD = FORM == FORM_FIELD && (MODE == K1_ITER || MODE == K1_FWD);
+  float2 pv[PF ? N2 : 1], pe[PF ? N2 : 1], pf[FIELD ? N2 : 1];
   const float2* v0t = a.V0 + vbase + t;   // this thread's elements are t + N1 m
   float2* et = a.E + ebase + t;
+
+  auto load_operands = [&]() {
+    if constexpr (PF) {
+      if (!ok) return;
+      if constexpr (FIELD)
+        sfor<0, N2>([&](auto M) { pf[CV(M)] = a.fin[ebase + t + N1 * CV(M)]; });
+      if (MODE == K1_FWD && a.green_in) return;
+      sfor<0, N2>([&](auto M) { pv[CV(M)] = v0t[N1 * CV(M)]; });
+      if (MODE != K1_FWD || a.warm) sfor<0, N2>([&](auto M) { pe[CV(M)] = et[N1 * CV(M)]; });
+    }
+  };
+  if constexpr (MODE == K1_FWD) load_operands();
 
   // element x of this thread's row in the bricks
   float2* wrow = wb + la * kBrick;
@@ -446,12 +464,7 @@ k1_xpass(CbsArgs a) {
       sfor<0, N1>([&](auto K1) { b[CV(K1)] = cmulc(b[CV(K1)], twt[CV(K1)]); });
       sfor<0, N1>([&](auto K1) { La[ta + N2 * CV(K1)] = b[CV(K1)]; });
     }
-  if constexpr (PF) {
-    if (ok) {
-      sfor<0, N2>([&](auto M) { pv[CV(M)] = v0t[N1 * CV(M)]; });
-      sfor<0, N2>([&](auto M) { pe[CV(M)] = et[N1 * CV(M)]; });
-    }
-  }
+    load_operands();
     __syncthreads();
     // inverse level B: thread k1 = t < N1, DFT-N2 over Lr[N2 k1 + j2]
     if (ok) {
@@ -485,48 +498,41 @@ k1_xpass(CbsArgs a) {
     const bool zin = (z >= a.pz) && (z < a.nz - a.pz);
     // pol_c exp(i (ky y + kz z)); the x phase joins per element when oblique
     const float2 ph = a.phase[(ib * 3 + c) * a.nz + z];
-    const float2 spl = OBL ? cmul(ph, a.phy[ib * a.ny + y]) : ph;
+    const float2 spl = FORM == FORM_OBLIQUE ? cmul(ph, a.phy[ib * a.ny + y]) : ph;
     const float2* phxb = a.phx + ib * a.nx;
+    const float fs = a.src_scale, fsi = a.src == SRC_FIELD_CONJ ? -fs : fs;
+    const bool green = MODE == K1_FWD && a.green_in;
     sfor<0, N2>([&](auto M) {
       const int x = t + N1 * CV(M);
-      float2 e;
-      float2 v0;
-      if constexpr (PF) v0 = pv[CV(M)]; else v0 = v0t[N1 * CV(M)];
-      if constexpr (MODE == K1_ITER) {
-        e = pe[CV(M)];
-        // gamma = 1 + i V0 / eps
-        const float2 gm = make_float2(1.0f - v0.y * a.inv_eps, v0.x * a.inv_eps);
-        const float2 d = cmul(gm, csub(v[CV(M)], e));
-        e = cadd(e, d);
-        sd += (double)(d.x * d.x + d.y * d.y);
-        se += (double)(e.x * e.x + e.y * e.y);
-        et[N1 * CV(M)] = e;
-      } else if (a.warm) {
-        e = et[N1 * CV(M)];
-      } else {
-        // cold start: E_s^(0) = 0, whatever the output buffer held
-        e = make_float2(0.f, 0.f);
-        if (!a.green_in) et[N1 * CV(M)] = e;
-      }
+      float2 e = make_float2(0.f, 0.f);   // a cold start, whatever the output buffer held
       float2 w;
-      if (MODE == K1_FWD && a.green_in) {
-        w = cscale(a.fin[ebase + x], a.src_scale);
+      if (FIELD && green) {
+        w = cscale(pf[FIELD ? CV(M) : 0], fs);
       } else {
+        const float2 v0 = pv[CV(M)];
+        if (MODE != K1_FWD || a.warm) e = pe[CV(M)];
+        if constexpr (MODE == K1_ITER) {
+          // gamma = 1 + i V0 / eps
+          const float2 gm = make_float2(1.0f - v0.y * a.inv_eps, v0.x * a.inv_eps);
+          const float2 d = cmul(gm, csub(v[CV(M)], e));
+          e = cadd(e, d);
+          sd += (double)(d.x * d.x + d.y * d.y);
+          se += (double)(e.x * e.x + e.y * e.y);
+        }
+        if (MODE == K1_ITER || !a.warm) et[N1 * CV(M)] = e;
         // W = (V0 - i eps) e + S
         w = cmul(make_float2(v0.x, v0.y - a.eps), e);
-        if (a.src == SRC_PLANE) {
+        if constexpr (FIELD) {
+          const float2 f = pf[CV(M)];
+          w = cadd(w, make_float2(f.x * fs, f.y * fsi));
+        } else if (a.src == SRC_PLANE) {
           const bool xin = (x >= a.px) && (x < a.nx - a.px);
           if (xin && yin && zin) {
-            if constexpr (OBL)
+            if constexpr (FORM == FORM_OBLIQUE)
               w = cadd(w, cmul(v0, cmul(spl, phxb[x])));
             else
               w = cadd(w, cmul(v0, spl));
           }
-        } else if (a.src == SRC_FIELD) {
-          w = cadd(w, cscale(a.fin[ebase + x], a.src_scale));
-        } else if (a.src == SRC_FIELD_CONJ) {
-          const float2 f = a.fin[ebase + x];
-          w = cadd(w, make_float2(f.x * a.src_scale, -f.y * a.src_scale));
         } else if (a.src == SRC_POINT) {
           if (x == a.r0x && y == a.r0y && z == a.r0z) w = cadd(w, a.st->amp[c]);
         }
@@ -658,7 +664,7 @@ struct XYGeom {
 };
 // MODE as in K1: K1_ITER the whole iteration, K1_FWD (W from E and the source, x
 // and y forward) and K1_RES (y and x inverse, fout = -gamma (GW - E)) its halves.
-template <int N1, int N2, int MODE, bool OBL>
+template <int N1, int N2, int MODE, int FORM>
 __global__ void __launch_bounds__((XYGeom<N1, N2>::THREADS), (XYGeom<N1, N2>::WAVES))
 kxy_pass(CbsArgs a) {
   using G = XYGeom<N1, N2>;
@@ -710,12 +716,15 @@ kxy_pass(CbsArgs a) {
   }
   // the pointwise operands of this thread's x-level-B tasks (y, k1): elements
   // x = k1 + N1 m of row y, in flight during the levels before them
-  float2 pv[G::QB][N2], pe[G::QB][N2];
+  constexpr bool FIELD = FORM == FORM_FIELD && MODE != K1_RES;
+  float2 pv[G::QB][N2], pe[G::QB][N2], pf[FIELD ? G::QB : 1][FIELD ? N2 : 1];
   sfor<0, G::QB>([&](auto QQ) {
     const int i = tid + CV(QQ) * T;
     if (i < N * N1) {
       const int o = (i / N1) * N + i % N1;
       sfor<0, N2>([&](auto M) { pv[CV(QQ)][CV(M)] = v0p[o + N1 * CV(M)]; });
+      if constexpr (FIELD)
+        sfor<0, N2>([&](auto M) { pf[CV(QQ)][CV(M)] = a.fin[ebase + o + N1 * CV(M)]; });
       if (MODE != K1_FWD || a.warm)
         sfor<0, N2>([&](auto M) { pe[CV(QQ)][CV(M)] = ep[o + N1 * CV(M)]; });
     }
@@ -752,6 +761,7 @@ kxy_pass(CbsArgs a) {
   // inverse x, level B; update; W = V E_s + S; forward x, level A'
   const bool zin = (z >= a.pz) && (z < a.nz - a.pz);
   const float2 ph = a.phase[(ib * 3 + c) * a.nz + z];   // pol_c exp(i kz z)
+  const float fs = a.src_scale, fsi = a.src == SRC_FIELD_CONJ ? -fs : fs;
   double sd = 0.0, se = 0.0;
   sfor<0, G::QB>([&](auto QQ) {
     const int i = tid + CV(QQ) * T;
@@ -774,7 +784,7 @@ kxy_pass(CbsArgs a) {
         return;
       }
       const bool yzin = zin && (y >= a.py) && (y < a.ny - a.py);
-      const float2 spl = OBL ? cmul(ph, a.phy[ib * a.ny + y]) : ph;
+      const float2 spl = FORM == FORM_OBLIQUE ? cmul(ph, a.phy[ib * a.ny + y]) : ph;
       const float2* phxb = a.phx + ib * a.nx;
       sfor<0, N2>([&](auto M) {
         const int x = t + N1 * CV(M);
@@ -790,18 +800,16 @@ kxy_pass(CbsArgs a) {
         }
         if (MODE == K1_ITER || !a.warm) ep[o + N1 * CV(M)] = e;
         float2 w = cmul(make_float2(v0.x, v0.y - a.eps), e);
-        if (a.src == SRC_PLANE) {
+        if constexpr (FIELD) {
+          const float2 f = pf[CV(QQ)][CV(M)];
+          w = cadd(w, make_float2(f.x * fs, f.y * fsi));
+        } else if (a.src == SRC_PLANE) {
           if (yzin && (x >= a.px) && (x < a.nx - a.px)) {
-            if constexpr (OBL)
+            if constexpr (FORM == FORM_OBLIQUE)
               w = cadd(w, cmul(v0, cmul(spl, phxb[x])));
             else
               w = cadd(w, cmul(v0, spl));
           }
-        } else if (a.src == SRC_FIELD) {
-          w = cadd(w, cscale(a.fin[ebase + o + N1 * CV(M)], a.src_scale));
-        } else if (a.src == SRC_FIELD_CONJ) {
-          const float2 f = a.fin[ebase + o + N1 * CV(M)];
-          w = cadd(w, make_float2(f.x * a.src_scale, -f.y * a.src_scale));
         } else if (a.src == SRC_POINT) {
           if (x == a.r0x && y == a.r0y && z == a.r0z) w = cadd(w, a.st->amp[c]);
         }
@@ -1082,7 +1090,7 @@ int k1_low_occupancy() {
   if (v < 0) {
     using G = XGeom<N1, N2>;
     int b = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k1_xpass<N1, N2, K1_ITER, false>, G::THREADS,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k1_xpass<N1, N2, K1_ITER, FORM_PLAIN>, G::THREADS,
                                                      0) != hipSuccess || b <= 0)
       v = 0;
     else
@@ -1091,25 +1099,38 @@ int k1_low_occupancy() {
   return v;
 }
 
+// the instantiation of a mode and source: go(mode, form)
+template <class F>
+void with_form(const CbsArgs& a, int mode, F&& go) {
+  using std::integral_constant;
+  auto forms = [&](auto MD) {
+    if (a.src == SRC_FIELD || a.src == SRC_FIELD_CONJ || a.green_in)
+      go(MD, integral_constant<int, FORM_FIELD>{});
+    else if (a.oblique && a.src == SRC_PLANE)
+      go(MD, integral_constant<int, FORM_OBLIQUE>{});
+    else
+      go(MD, integral_constant<int, FORM_PLAIN>{});
+  };
+  if (mode == K1_FWD)
+    forms(integral_constant<int, K1_FWD>{});
+  else if (mode == K1_ITER)
+    forms(integral_constant<int, K1_ITER>{});
+  else if (mode == K1_RES)
+    go(integral_constant<int, K1_RES>{}, integral_constant<int, FORM_PLAIN>{});
+  else
+    go(integral_constant<int, K1_INV>{}, integral_constant<int, FORM_PLAIN>{});
+}
+
 template <int N1, int N2>
 void launch_k1(const CbsArgs& a_in, int mode, hipStream_t s) {
   using G = XGeom<N1, N2>;
   CbsArgs a = a_in;
   a.k1_prio = k1_low_occupancy<N1, N2>();
   const unsigned nb = 3u * (unsigned)a.nb * (unsigned)a.gy * (unsigned)a.nz;
-  const bool obl = a.oblique && a.src == SRC_PLANE;
-  if (mode == K1_FWD && !obl)
-    hipLaunchKernelGGL((k1_xpass<N1, N2, K1_FWD, false>), dim3(nb), dim3(G::THREADS), 0, s, a);
-  else if (mode == K1_FWD)
-    hipLaunchKernelGGL((k1_xpass<N1, N2, K1_FWD, true>), dim3(nb), dim3(G::THREADS), 0, s, a);
-  else if (mode == K1_ITER && !obl)
-    hipLaunchKernelGGL((k1_xpass<N1, N2, K1_ITER, false>), dim3(nb), dim3(G::THREADS), 0, s, a);
-  else if (mode == K1_ITER)
-    hipLaunchKernelGGL((k1_xpass<N1, N2, K1_ITER, true>), dim3(nb), dim3(G::THREADS), 0, s, a);
-  else if (mode == K1_RES)
-    hipLaunchKernelGGL((k1_xpass<N1, N2, K1_RES, false>), dim3(nb), dim3(G::THREADS), 0, s, a);
-  else
-    hipLaunchKernelGGL((k1_xpass<N1, N2, K1_INV, false>), dim3(nb), dim3(G::THREADS), 0, s, a);
+  auto go = [&](auto MD, auto FM) {
+    hipLaunchKernelGGL((k1_xpass<N1, N2, CV(MD), CV(FM)>), dim3(nb), dim3(G::THREADS), 0, s, a);
+  };
+  with_form(a, mode, go);
 }
 
 template <int N1, int N2>
@@ -1151,17 +1172,10 @@ template <int N1, int N2>
 void launch_kxy(const CbsArgs& a, int mode, hipStream_t s) {
   using G = XYGeom<N1, N2>;
   const dim3 grid(3u * (unsigned)a.nb * (unsigned)a.nz), block(G::THREADS);
-  const bool obl = a.oblique && a.src == SRC_PLANE;
-  if (mode == K1_RES)
-    hipLaunchKernelGGL((kxy_pass<N1, N2, K1_RES, false>), grid, block, 0, s, a);
-  else if (mode == K1_FWD && obl)
-    hipLaunchKernelGGL((kxy_pass<N1, N2, K1_FWD, true>), grid, block, 0, s, a);
-  else if (mode == K1_FWD)
-    hipLaunchKernelGGL((kxy_pass<N1, N2, K1_FWD, false>), grid, block, 0, s, a);
-  else if (obl)
-    hipLaunchKernelGGL((kxy_pass<N1, N2, K1_ITER, true>), grid, block, 0, s, a);
-  else
-    hipLaunchKernelGGL((kxy_pass<N1, N2, K1_ITER, false>), grid, block, 0, s, a);
+  with_form(a, mode, [&](auto MD, auto FM) {
+    if constexpr (CV(MD) != K1_INV)   // cbs_apply_green's x pass has no plane form
+      hipLaunchKernelGGL((kxy_pass<N1, N2, CV(MD), CV(FM)>), grid, block, 0, s, a);
+  });
 }
 // the fused plane pass needs a plane of N x N complex values in 160 KB of LDS
 template <int N1, int N2>
