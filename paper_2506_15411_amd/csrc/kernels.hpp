@@ -382,8 +382,7 @@ k1_xpass(CbsArgs a) {
   __shared__ float2 lds[R * N];     // R rows of one component, natural x order
   __shared__ double red[2 * (G::THREADS / 64)];
 
-  if (MODE == K1_ITER && a.st->done) return;
-
+  const int done = MODE == K1_ITER ? a.st->done : 0;
   const int tid = threadIdx.x;
   // with few waves per SIMD, a work-group's load phase would otherwise wait
   // behind the other waves' vector work
@@ -452,6 +451,10 @@ k1_xpass(CbsArgs a) {
     if (oka) sfor<0, N1>([&](auto J1) { b[CV(J1)] = wat(ta + N2 * CV(J1)); });
   };
   if constexpr (MODE != K1_FWD) load_a();
+  if constexpr (MODE == K1_ITER) {
+    asm volatile("" ::: "memory");   // the loads are issued before the flag is waited for
+    if (done) return;
+  }
   tws.commit(tw, tid);
   __syncthreads();   // the twiddle table is in LDS
   if (a.k1_prio) __builtin_amdgcn_s_setprio(0);
@@ -569,7 +572,7 @@ ky_pass(CbsArgs a) {
   constexpr int N = G::N;
   __shared__ float2 lds[N * TX];
   __shared__ float2 tw[N];
-  if (a.st->done) return;
+  const int done = a.st->done;
   const int tid = threadIdx.x;
   if (a.ky_prio) __builtin_amdgcn_s_setprio(kLoadPrio);
   TwStage<N, G::THREADS> tws;
@@ -602,6 +605,8 @@ ky_pass(CbsArgs a) {
     }
   };
   load_a();
+  asm volatile("" ::: "memory");   // the loads are issued before the flag is waited for
+  if (done) return;
   tws.commit(tw, tid);
   __syncthreads();
   if (a.ky_prio) __builtin_amdgcn_s_setprio(0);
@@ -672,7 +677,7 @@ kxy_pass(CbsArgs a) {
   __shared__ float2 lds[N * P];
   __shared__ float2 tw[N];
   __shared__ double red[2 * (T / 64)];
-  if (MODE == K1_ITER && a.st->done) return;
+  const int done = MODE == K1_ITER ? a.st->done : 0;
   const int tid = threadIdx.x;
   TwStage<N, T> tws;
   tws.issue(a.twx, tid);
@@ -701,6 +706,11 @@ kxy_pass(CbsArgs a) {
         sfor<0, N1>([&](auto J) { b[CV(QQ)][CV(J)] = w[N2 * kBrick * CV(J)]; });
       }
     });
+    // The stop flag, read first, is waited for behind the issued loads, here and in
+    // the other passes: one round trip less per launch (16^3 iteration 8.5 -> 7.9
+    // us, 32^3 10.9 -> 10.1, 64^3 19.5 -> 19.1, 275 x 275 x 315 1200 -> 1194).
+    asm volatile("" ::: "memory");
+    if (done) return;
     tws.commit(tw, tid);
     __syncthreads();
     sfor<0, G::QG>([&](auto QQ) {
@@ -877,12 +887,12 @@ kz_pass(CbsArgs a) {
   constexpr int N = G::N;
   __shared__ float2 lds[3 * N * TX];
   __shared__ float2 tw[N];
-  if (a.st->done) return;
+  const int done = a.st->done;
   // block 0 transforms nothing: it finishes the previous iteration's residual
   // (stream order: the x pass that wrote the partials has completed) beside the
   // columns of the others
   if (blockIdx.x == 0) {
-    if (!a.st->pending) return;
+    if (done || !a.st->pending) return;
     constexpr bool kFits = sizeof(lds) >= 2 * kResStreams * sizeof(double);
     if constexpr (kFits) {
       residual_finish<G::THREADS>(a.partials, a.k1_blocks, a.nb, a.st, a.hist,
@@ -932,6 +942,8 @@ kz_pass(CbsArgs a) {
     }
   };
   load_a();
+  asm volatile("" ::: "memory");   // the loads are issued before the flag is waited for
+  if (done) return;
   tws.commit(tw, tid);
   __syncthreads();
   if (t < 3 * N2) {
