@@ -98,15 +98,12 @@ __device__ __forceinline__ double ipow(double u, int m) {
 __global__ void __launch_bounds__(kSetupThreads) k_setup(SetupArgs a) {
   __shared__ double smx[kSetupThreads / 64];
   __shared__ unsigned sfl[kSetupThreads / 64];
-  const long long N = (long long)a.nx * a.ny * a.nz;
+  const unsigned N = (unsigned)a.nx * a.ny * a.nz;   // below 2^29: 32-bit index arithmetic
   double mx = 0.0;
   unsigned fl = 0;
-  for (long long i = (long long)blockIdx.x * kSetupThreads + threadIdx.x; i < N;
-       i += (long long)gridDim.x * kSetupThreads) {
-    const int x = (int)(i % a.nx);
-    const long long r = i / a.nx;
-    const int y = (int)(r % a.ny);
-    const int z = (int)(r / a.ny);
+  for (unsigned i = blockIdx.x * kSetupThreads + threadIdx.x; i < N; i += gridDim.x * kSetupThreads) {
+    const unsigned r = i / (unsigned)a.nx;
+    const int x = (int)(i - r * a.nx), y = (int)(r % (unsigned)a.ny), z = (int)(r / (unsigned)a.ny);
     float er, ei;
     if (a.dtype == CBS_F32) {
       er = static_cast<const float*>(a.eps)[i];
@@ -166,6 +163,11 @@ __global__ void k_state_init(DevState* st, double tol, int max_iter, int record)
   }
 }
 
+// w[0, n) = 0
+__global__ void k_clear_words(unsigned* w, int n) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) w[i] = 0u;
+}
+
 // point-source amplitude: conj(E(r0)) * scale (from_field) or given * scale
 __global__ void k_point_amp(DevState* st, const float2* E, long long idx, long long sE,
                             int from_field, float scale, float2 g0, float2 g1, float2 g2) {
@@ -195,19 +197,20 @@ k_residual(const double* part, int per_b, int nb, DevState* st, double* hist) {
 }
 
 // E_b += sign * pol_b exp(i k_b . r) for every illumination b of a solve
-// (the incident plane waves; normal incidence: pol exp(i kb z))
+// (the incident plane waves; normal incidence: pol exp(i kb z)).  Components the
+// polarisation leaves at zero are not touched: an x-polarised wave reads and
+// writes 16 bytes a voxel instead of 48 (275 x 275 x 315: 200 -> 62 us).
 __global__ void k_incident(CbsArgs a, float sign) {
-  const long long N = (long long)a.nx * a.ny * a.nz;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < N;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int x = (int)(i % a.nx);
-    const int y = (int)((i / a.nx) % a.ny);
-    const int z = (int)(i / ((long long)a.nx * a.ny));
+  const unsigned N = (unsigned)a.nx * a.ny * a.nz;   // below 2^29: 32-bit index arithmetic
+  for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < N; i += gridDim.x * blockDim.x) {
+    const unsigned l = i / (unsigned)a.nx;
+    const int x = (int)(i - l * a.nx), y = (int)(l % (unsigned)a.ny), z = (int)(l / (unsigned)a.ny);
     for (int b = 0; b < a.nb; ++b) {
       const float2 pxy = a.oblique ? cmul(a.phy[b * a.ny + y], a.phx[b * a.nx + x])
                                    : make_float2(1.f, 0.f);
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
+        if (!((a.pol_mask >> (3 * b + c)) & 1u)) continue;
         const float2 pz = a.phase[(b * 3 + c) * a.nz + z];
         const float2 inc = a.oblique ? cmul(pz, pxy) : pz;
         float2* ep = a.E + b * a.sEb + c * a.sE + i;
@@ -254,13 +257,10 @@ __global__ void k_phase_tables(float2* phx, float2* phy, float2* phz, int nx, in
 __global__ void k_gradient(const float2* E, const float2* Ea, long long sE, int nx, int ny,
                            int x0, int y0, int z0, int bx, int by, int bz, double scale,
                            float* grad) {
-  const long long NB = (long long)bx * by * bz;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < NB;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int xi = (int)(i % bx);
-    const long long r = i / bx;
-    const int yi = (int)(r % by);
-    const int zi = (int)(r / by);
+  const unsigned NB = (unsigned)bx * by * bz;   // below 2^29: 32-bit index arithmetic
+  for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < NB; i += gridDim.x * blockDim.x) {
+    const unsigned r = i / (unsigned)bx;
+    const int xi = (int)(i - r * bx), yi = (int)(r % (unsigned)by), zi = (int)(r / (unsigned)by);
     const long long idx = ((long long)(z0 + zi) * ny + (y0 + yi)) * nx + (x0 + xi);
     double s = 0.0;
 #pragma unroll
@@ -515,54 +515,68 @@ __device__ __forceinline__ int tfsf_axis(const TfsfArgs& t, int j, int& i) {
   return a;
 }
 
-// f and its DFT (one thread per axis entry)
-__global__ void k_tfsf_forward(TfsfArgs t) {
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < t.ntot; j += gridDim.x * blockDim.x) {
-    int m;
-    const int a = tfsf_axis(t, j, m);
-    const int n = t.n[a];
-    double re = 0.0, im = 0.0;
-    for (int i = t.lo[a]; i < t.hi[a]; ++i) {   // f vanishes outside the box
-      double sf, cf, sw, cw;
-      sincos(t.kd[a] * (double)i, &sf, &cf);
-      sincos(-2.0 * M_PI * (double)(((long long)m * i) % n) / (double)n, &sw, &cw);
-      re += cf * cw - sf * sw;
-      im += cf * sw + sf * cw;
-    }
-    t.tab[t.ntot + j] = make_double2(re, im);
-    double sf = 0.0, cf = 0.0;
-    if (m >= t.lo[a] && m < t.hi[a]) sincos(t.kd[a] * (double)m, &sf, &cf);
-    t.tab[j] = make_double2(cf, sf);
-  }
+__device__ __forceinline__ double wave_sum(double v) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
 }
 
-// the three filtered inverse transforms (one thread per axis entry)
-__global__ void k_tfsf_inverse(TfsfArgs t) {
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < t.ntot; j += gridDim.x * blockDim.x) {
-    int i;
-    const int a = tfsf_axis(t, j, i);
-    const int n = t.n[a];
-    double r2 = 0.0, i2 = 0.0, r1 = 0.0, i1 = 0.0, rt = 0.0, it = 0.0;
-    for (int m = 0; m < n; ++m) {
-      const double2 F = t.tab[t.ntot + t.off[a] + m];
-      const int mm = (m < (n + 1) / 2) ? m : m - n;
-      const double pm = 2.0 * M_PI * (double)mm / ((double)n * t.pitch);
-      const double ptm = ((n & 1) == 0 && 2 * m == n) ? 0.0 : pm;
-      double sw, cw;
-      sincos(2.0 * M_PI * (double)(((long long)m * i) % n) / (double)n, &sw, &cw);
-      const double gr = F.x * cw - F.y * sw, gi = F.x * sw + F.y * cw;   // F(m) e^{+2 pi i m i/n}
-      r2 += pm * pm * gr;
-      i2 += pm * pm * gi;
-      r1 += ptm * gr;
-      i1 += ptm * gi;
-      rt += ptm * ptm * gr;
-      it += ptm * ptm * gi;
-    }
-    const double inv = 1.0 / (double)n;
-    t.tab[2 * t.ntot + j] = make_double2(r2 * inv, i2 * inv);
-    t.tab[3 * t.ntot + j] = make_double2(r1 * inv, i1 * inv);
-    t.tab[4 * t.ntot + j] = make_double2(rt * inv, it * inv);
+// f and its DFT: one wave per axis entry, its lanes share the sum (one thread per
+// entry, a serial chain of two sincos per term, took 80 us on 192 x 192 x 256)
+__global__ void __launch_bounds__(64) k_tfsf_forward(TfsfArgs t) {
+  const int j = blockIdx.x, lane = threadIdx.x;
+  int m;
+  const int a = tfsf_axis(t, j, m);
+  const int n = t.n[a];
+  double re = 0.0, im = 0.0;
+  for (int i = t.lo[a] + lane; i < t.hi[a]; i += 64) {   // f vanishes outside the box
+    double sf, cf, sw, cw;
+    sincos(t.kd[a] * (double)i, &sf, &cf);
+    sincos(-2.0 * M_PI * (double)((m * i) % n) / (double)n, &sw, &cw);
+    re += cf * cw - sf * sw;
+    im += cf * sw + sf * cw;
   }
+  re = wave_sum(re);
+  im = wave_sum(im);
+  if (lane != 0) return;
+  t.tab[t.ntot + j] = make_double2(re, im);
+  double sf = 0.0, cf = 0.0;
+  if (m >= t.lo[a] && m < t.hi[a]) sincos(t.kd[a] * (double)m, &sf, &cf);
+  t.tab[j] = make_double2(cf, sf);
+}
+
+// the three filtered inverse transforms, one wave per axis entry
+__global__ void __launch_bounds__(64) k_tfsf_inverse(TfsfArgs t) {
+  const int j = blockIdx.x, lane = threadIdx.x;
+  int i;
+  const int a = tfsf_axis(t, j, i);
+  const int n = t.n[a];
+  double r2 = 0.0, i2 = 0.0, r1 = 0.0, i1 = 0.0, rt = 0.0, it = 0.0;
+  for (int m = lane; m < n; m += 64) {
+    const double2 F = t.tab[t.ntot + t.off[a] + m];
+    const int mm = (m < (n + 1) / 2) ? m : m - n;
+    const double pm = 2.0 * M_PI * (double)mm / ((double)n * t.pitch);
+    const double ptm = ((n & 1) == 0 && 2 * m == n) ? 0.0 : pm;
+    double sw, cw;
+    sincos(2.0 * M_PI * (double)((m * i) % n) / (double)n, &sw, &cw);
+    const double gr = F.x * cw - F.y * sw, gi = F.x * sw + F.y * cw;   // F(m) e^{+2 pi i m i/n}
+    r2 += pm * pm * gr;
+    i2 += pm * pm * gi;
+    r1 += ptm * gr;
+    i1 += ptm * gi;
+    rt += ptm * ptm * gr;
+    it += ptm * ptm * gi;
+  }
+  const double inv = 1.0 / (double)n;
+  r2 = wave_sum(r2) * inv;
+  i2 = wave_sum(i2) * inv;
+  r1 = wave_sum(r1) * inv;
+  i1 = wave_sum(i1) * inv;
+  rt = wave_sum(rt) * inv;
+  it = wave_sum(it) * inv;
+  if (lane != 0) return;
+  t.tab[2 * t.ntot + j] = make_double2(r2, i2);
+  t.tab[3 * t.ntot + j] = make_double2(r1, i1);
+  t.tab[4 * t.ntot + j] = make_double2(rt, it);
 }
 
 // zmul: complex FP64 product (scpml.hpp)
@@ -582,16 +596,14 @@ struct TfsfAssemble {
 //       - sum_b q_b T_c T_b u   (T_c T_b u = (T1 f)(T1 f)(f) for c != b, (T2 f)(f)(f) for c = b)
 __global__ void k_tfsf_assemble(TfsfAssemble A) {
   const TfsfArgs& t = A.t;
-  const long long N = (long long)A.nx * A.ny * A.nz;
+  const unsigned N = (unsigned)A.nx * A.ny * A.nz;   // below 2^29: 32-bit index arithmetic
   const double2* f = t.tab;
   const double2* d2 = t.tab + 2 * t.ntot;
   const double2* t1 = t.tab + 3 * t.ntot;
   const double2* t2 = t.tab + 4 * t.ntot;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < N;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int x = (int)(i % A.nx);
-    const int y = (int)((i / A.nx) % A.ny);
-    const int z = (int)(i / ((long long)A.nx * A.ny));
+  for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < N; i += gridDim.x * blockDim.x) {
+    const unsigned l = i / (unsigned)A.nx;
+    const int x = (int)(i - l * A.nx), y = (int)(l % (unsigned)A.ny), z = (int)(l / (unsigned)A.ny);
     const int ix = t.off[0] + x, iy = t.off[1] + y, iz = t.off[2] + z;
     const double2 u = zmul3(f[ix], f[iy], f[iz]);
     const double su = ipow(layer_depth(x, A.nx, A.px), A.order) +
@@ -634,7 +646,7 @@ __global__ void k_tfsf_assemble(TfsfAssemble A) {
         sc.x -= w.x;
         sc.y -= w.y;
       }
-      A.S[c * N + i] = make_float2((float)sc.x, (float)sc.y);
+      A.S[(size_t)c * N + i] = make_float2((float)sc.x, (float)sc.y);
     }
   }
 }
@@ -1183,6 +1195,8 @@ int set_plane_wave(cbs_plan_s* p, CbsArgs& a, Kvec& kv, int b, const cbs_source*
   }
   if (!std::isfinite(sx) || !std::isfinite(sy) || !(sx * sx + sy * sy < 1.0))
     return fail(CBS_E_INVALID, "plane-wave direction (%g, %g): need sx^2 + sy^2 < 1", sx, sy);
+  for (int c = 0; c < 3; ++c)
+    if (kv.pol[b][c][0] != 0.0 || kv.pol[b][c][1] != 0.0) a.pol_mask |= 1u << (3 * b + c);
   const double kbd = p->kb * p->pitch;
   kv.kd[b][0] = kbd * sx;
   kv.kd[b][1] = kbd * sy;
@@ -1268,10 +1282,6 @@ int static_scratch(void** out) {
   }
   *out = g_scratch_ptr[dev];
   return CBS_OK;
-}
-
-__global__ void k_clear_words(unsigned* w, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) w[i] = 0u;
 }
 
 // The blocking solve loop without events or a pinned ring: enqueue
@@ -1782,7 +1792,7 @@ int cbs_tfsf_source(cbs_plan_t p, const cbs_source* src, const int lo[3], const 
     A.q[c] = make_double2(re, im);
   }
   A.S = static_cast<float2*>(S_dev);
-  const dim3 g1((t.ntot + 127) / 128), b1(128);
+  const dim3 g1(t.ntot), b1(64);
   hipLaunchKernelGGL(k_tfsf_forward, g1, b1, 0, p->stream, t);
   HIP_LAUNCHED();
   hipLaunchKernelGGL(k_tfsf_inverse, g1, b1, 0, p->stream, t);

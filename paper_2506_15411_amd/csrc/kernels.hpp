@@ -206,6 +206,7 @@ struct CbsArgs {
   long long sWb, sEb;           // stride between illuminations in W (3 sW) and E (3 sE)
   const float2* phx;            // [nb][nx] exp(i kx d x) of each illumination's plane wave
   const float2* phy;            // [nb][ny] exp(i ky d y)
+  unsigned pol_mask;            // bit 3 b + c: illumination b's polarisation has a component c
   int oblique;                  // some illumination has kx or ky != 0 (phx, phy not all 1)
   int k1_prio;                  // x-pass: raise wave priority for the load phase (set by launch_k1)
   int ky_prio;                  // y pass: the same (set by launch_ky)
