@@ -680,6 +680,7 @@ struct cbs_plan_s {
   // workspace carve-up
   float2 *W, *V0, *twx, *twy, *twz, *phase, *phx, *phy;
   double *partials, *setup_part, *hist, *metrics;
+  unsigned char* rows;   // zero rows of a field source (CbsArgs::rows)
   DevState* state;
   bool have_eps;
   double eps;  // 1/m^2
@@ -714,7 +715,7 @@ static __device__ __align__(256) unsigned char cbs_scratch[CBS_STATIC_SCRATCH_BY
 namespace {
 
 struct Layout {
-  size_t W, V0, twx, twy, twz, phase, phx, phy, partials, setup, hist, metrics, state, total;
+  size_t W, V0, twx, twy, twz, phase, phx, phy, partials, setup, hist, metrics, rows, state, total;
 };
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -745,7 +746,8 @@ bool layout_of(int nx, int ny, int nz, Layout& L) {
   L.setup = take((size_t)2 * kSetupBlocks * sizeof(double));
   L.hist = take((size_t)kHistCap * sizeof(double));
   L.metrics = take((size_t)(2 * kMetricBlocks + 2 + nx + ny + nz + 1) * sizeof(double) +
-                   (size_t)(nx + ny + 4 * N / nz) * sizeof(double2));
+                   (size_t)(nx + ny + 5 * N / nz) * sizeof(double2));
+  L.rows = take((size_t)3 * nz * ny);
   L.state = take(sizeof(DevState));
   L.total = off;
   return true;
@@ -824,6 +826,7 @@ void init_plan(cbs_plan_s* p, int nx, int ny, int nz, double pitch_m, double lam
   p->setup_part = reinterpret_cast<double*>(base + L.setup);
   p->hist = reinterpret_cast<double*>(base + L.hist);
   p->metrics = reinterpret_cast<double*>(base + L.metrics);
+  p->rows = reinterpret_cast<unsigned char*>(base + L.rows);
   p->state = reinterpret_cast<DevState*>(base + L.state);
   p->have_eps = false;
   p->eps = -1.0;
@@ -1048,6 +1051,13 @@ int begin_solve(cbs_plan_s* p, CbsArgs& a, const cbs_opts* o, const cbs_source* 
   if (int rc = enqueue_solve_start(p, a, o, src, E_fwd, kv)) return rc;
   const bool plane = a.src == SRC_PLANE;
   HIP_TRY(hipEventRecord(p->ev0, p->stream));
+  if (!a.fused && (a.src == SRC_FIELD || a.src == SRC_FIELD_CONJ)) {
+    a.rows = p->rows;   // 256-byte aligned and padded: cleared in words
+    const int words = (3 * p->nz * p->ny + 3) / 4;
+    hipLaunchKernelGGL(k_clear_words, dim3((words + 255) / 256), dim3(256), 0, p->stream,
+                       reinterpret_cast<unsigned*>(a.rows), words);
+    HIP_LAUNCHED();
+  }
   enqueue_prologue(p, a);
   HIP_LAUNCHED();
   A.on = true;

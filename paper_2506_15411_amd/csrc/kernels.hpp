@@ -198,6 +198,8 @@ struct CbsArgs {
   const float2* twz;            // same layout for the z split
   const float2* phase;          // [nb][3][nz] pol_c exp(i kz d z) of each illumination's wave
   const float2* fin;            // FIELD source / Green input
+  unsigned char* rows;          // FIELD source: [3][nz][ny], 0 for rows of the field that are
+                                // all zero (written by the prologue); null: not kept
   float2* fout;                 // Green output
   double* partials;             // 2 doubles per K1 block
   int k1_blocks;                // K1 or KXY blocks per illumination (partials to reduce)
@@ -431,11 +433,18 @@ k1_xpass(CbsArgs a) {
   const float2* v0t = a.V0 + vbase + t;   // this thread's elements are t + N1 m
   float2* et = a.E + ebase + t;
 
+  // a field source that is zero along the row is not read again every iteration
+  // (the source of an objective at a point or in a plane: x pass of 189 x 189 x 121
+  // 102 us with the field read, 70 without)
+  const long long frow = ((long long)c * a.nz + z) * a.ny + y;
+  const bool live = !(FIELD && MODE == K1_ITER) || !a.rows || a.rows[frow];
   auto load_operands = [&]() {
     if constexpr (PF) {
       if (!ok) return;
-      if constexpr (FIELD)
-        sfor<0, N2>([&](auto M) { pf[CV(M)] = a.fin[ebase + t + N1 * CV(M)]; });
+      if constexpr (FIELD) {
+        sfor<0, N2>([&](auto M) { pf[CV(M)] = make_float2(0.f, 0.f); });
+        if (live) sfor<0, N2>([&](auto M) { pf[CV(M)] = a.fin[ebase + t + N1 * CV(M)]; });
+      }
       if (MODE == K1_FWD && a.green_in) return;
       sfor<0, N2>([&](auto M) { pv[CV(M)] = v0t[N1 * CV(M)]; });
       if (MODE != K1_FWD || a.warm) sfor<0, N2>([&](auto M) { pe[CV(M)] = et[N1 * CV(M)]; });
@@ -506,6 +515,11 @@ k1_xpass(CbsArgs a) {
     const float2* phxb = a.phx + ib * a.nx;
     const float fs = a.src_scale, fsi = a.src == SRC_FIELD_CONJ ? -fs : fs;
     const bool green = MODE == K1_FWD && a.green_in;
+    if constexpr (FIELD && MODE == K1_FWD) {
+      bool any = false;
+      sfor<0, N2>([&](auto M) { any |= pf[CV(M)].x != 0.f || pf[CV(M)].y != 0.f; });
+      if (any && a.rows) a.rows[frow] = 1;   // every thread that writes writes 1
+    }
     sfor<0, N2>([&](auto M) {
       const int x = t + N1 * CV(M);
       float2 e = make_float2(0.f, 0.f);   // a cold start, whatever the output buffer held
