@@ -2033,14 +2033,15 @@ int enqueue_delta(const Scpml& s, const float2* v, float2* F, float alpha) {
 // w = B v = v - (the CBS step from v with the field source -(L_s - L) v):
 // B = gamma [I - G (V - (L_s - L))], the CBS-preconditioned stretched operator.
 // v minus its step is the negative of the step's update, which the x pass writes
-// to w itself (K1_RES): v is neither copied nor subtracted from.
-int enqueue_operator(const Scpml& s, const float2* v, float2* w) {
+// to w itself (K1_RES): v is neither copied nor subtracted from.  w = scale B v.
+int enqueue_operator(const Scpml& s, const float2* v, float2* w, double scale) {
   cbs_plan_s* p = s.p;
   int rc = enqueue_delta(s, v, s.F, -1.0f);
   if (rc) return rc;
   CbsArgs a = base_args(p);
   a.E = const_cast<float2*>(v);   // read only: warm prologue and K1_RES
   a.fout = w;
+  a.res_scale = (float)scale;
   a.src = SRC_FIELD;
   a.fin = s.F;
   a.src_scale = 1.0f;   // F is already in units of the pitch
@@ -2071,11 +2072,11 @@ int enqueue_dots(const Scpml& s, const float2* V, int cnt, const float2* w, doub
   return CBS_OK;
 }
 
-// w += sign sum_i c_i V_i; with norm, *norm = |w|^2 afterwards
-int enqueue_update(const Scpml& s, int cnt, const double2* c, float sign, float2* w,
-                   double2* norm = nullptr) {
+// w += sign sum_i c_i / nrm_i V_i (nrm null: 1); with norm, *norm = |w|^2 afterwards
+int enqueue_update(const Scpml& s, int cnt, const double2* c, const double2* nrm, float sign,
+                   float2* w, double2* norm = nullptr) {
   hipLaunchKernelGGL(k_gm_update, dim3(kGmUpdateBlocks), dim3(kGmThreads), 0, s.p->stream, s.basis,
-                     s.n3, cnt, c, sign, w, s.n3, norm ? s.part : nullptr);
+                     s.n3, cnt, c, nrm, sign, w, s.n3, norm ? s.part : nullptr);
   HIP_LAUNCHED();
   if (norm) {
     hipLaunchKernelGGL(k_gm_dots_finish, dim3(1), dim3(kGmThreads), 0, s.p->stream, s.part,
@@ -2085,10 +2086,10 @@ int enqueue_update(const Scpml& s, int cnt, const double2* c, float sign, float2
   return CBS_OK;
 }
 
-int enqueue_scale(const Scpml& s, float2* w, double f) {
+int enqueue_scale(const Scpml& s, float2* w, double f, double2* nrm) {
   dim3 g;
   gm_grid(s.n3, g);
-  hipLaunchKernelGGL(k_gm_scale, g, dim3(kGmThreads), 0, s.p->stream, w, s.n3, (float)f);
+  hipLaunchKernelGGL(k_gm_scale, g, dim3(kGmThreads), 0, s.p->stream, w, s.n3, (float)f, nrm);
   HIP_LAUNCHED();
   return CBS_OK;
 }
@@ -2103,6 +2104,9 @@ int read_back(cbs_plan_s* p, const double2* dev, std::complex<double>* host, int
 // Restarted GMRES(m) on B x = b from x = 0 (x in E_dev).  Arnoldi with
 // classical Gram-Schmidt (fused dot and update passes over the basis),
 // repeated for a step whose projection shortened w more than tenfold;
+// V_j of a step is kept as the update leaves it, with its length: 1 / |V_j| goes
+// into the operator's output, the dots and the coefficients instead of a pass
+// over the vector (0.2 of 9.8 ms a step at 275 x 275 x 315);
 // Givens rotations on the host in FP64; at the end of each cycle the true
 // residual b - B x gives the restart vector and the reported residual.
 int scpml_gmres(const Scpml& s, float2* x, int m, const cbs_opts* o, double beta0, int* iters,
@@ -2110,6 +2114,10 @@ int scpml_gmres(const Scpml& s, float2* x, int m, const cbs_opts* o, double beta
   cbs_plan_s* p = s.p;
   using cd = std::complex<double>;
   std::vector<cd> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), hv(3 * (m + 1)), y(m + 1);
+  std::vector<double> sig(m + 1, 1.0);   // 1 / |V_j|
+  double2* h0 = s.h;                     // V^H w
+  double2* h1 = s.h + (m + 1);           // the second projection's
+  double2* nrm = s.h + 2 * (m + 1);      // |V_j|^2
   auto Hij = [&](int i, int j) -> cd& { return H[(size_t)j * (m + 1) + i]; };
   int total = 0, rc;
   double beta = beta0, rel = 1.0;
@@ -2118,33 +2126,30 @@ int scpml_gmres(const Scpml& s, float2* x, int m, const cbs_opts* o, double beta
   gm_grid(s.n3, gg);
   hipLaunchKernelGGL(k_gm_copy, gg, dim3(kGmThreads), 0, p->stream, s.b, s.vec(0), s.n3);
   HIP_LAUNCHED();
-  if ((rc = enqueue_scale(s, s.vec(0), 1.0 / beta0))) return rc;
+  if ((rc = enqueue_scale(s, s.vec(0), 1.0 / beta0, nrm))) return rc;
   while (true) {
     std::fill(g.begin(), g.end(), cd(0));
     g[0] = beta;
     int k = 0;
     for (int j = 0; j < m && total < o->max_iter; ++j) {
       float2* w = s.vec(j + 1);
-      if ((rc = enqueue_operator(s, s.vec(j), w))) return rc;
-      double2* h0 = s.h;
-      double2* h1 = s.h + (m + 1);
-      double2* h2 = s.h + 2 * (m + 1);
+      if ((rc = enqueue_operator(s, s.vec(j), w, sig[j]))) return rc;
       // classical Gram-Schmidt; the sweep over V_0..V_j also gives |w|^2 before
       // the projection (h0[j+1]), the update |w|^2 after it
       if ((rc = enqueue_dots(s, s.basis, j + 1, w, h0, true))) return rc;
-      if ((rc = enqueue_update(s, j + 1, h0, -1.0f, w, h2))) return rc;
+      if ((rc = enqueue_update(s, j + 1, h0, nrm, -1.0f, w, nrm + j + 1))) return rc;
       if ((rc = read_back(p, s.h, hv.data(), 3 * (m + 1)))) return rc;
-      for (int i = 0; i <= j; ++i) Hij(i, j) = hv[i];
-      double nn = hv[2 * (m + 1)].real();
+      for (int i = 0; i <= j; ++i) Hij(i, j) = sig[i] * hv[i];
+      double nn = hv[2 * (m + 1) + j + 1].real();
       // the projection shortened w more than tenfold: FP32 rounding of the
       // update may have left components along the basis of about 10 ulp of the
       // original length, so project once more (a DGKS-type test)
       if (nn < 1e-2 * hv[j + 1].real()) {
         if ((rc = enqueue_dots(s, s.basis, j + 1, w, h1))) return rc;
-        if ((rc = enqueue_update(s, j + 1, h1, -1.0f, w, h2))) return rc;
+        if ((rc = enqueue_update(s, j + 1, h1, nrm, -1.0f, w, nrm + j + 1))) return rc;
         if ((rc = read_back(p, s.h, hv.data(), 3 * (m + 1)))) return rc;
-        for (int i = 0; i <= j; ++i) Hij(i, j) += hv[(m + 1) + i];
-        nn = hv[2 * (m + 1)].real();
+        for (int i = 0; i <= j; ++i) Hij(i, j) += sig[i] * hv[(m + 1) + i];
+        nn = hv[2 * (m + 1) + j + 1].real();
       }
       const double hn = std::sqrt(std::max(0.0, nn));
       Hij(j + 1, j) = hn;
@@ -2152,7 +2157,7 @@ int scpml_gmres(const Scpml& s, float2* x, int m, const cbs_opts* o, double beta
         if (!std::isfinite(Hij(i, j).real()) || !std::isfinite(Hij(i, j).imag()))
           return fail(CBS_E_DIVERGED, "non-finite Arnoldi coefficient after %d steps", total);
       if (!std::isfinite(hn)) return fail(CBS_E_DIVERGED, "non-finite norm after %d steps", total);
-      if (hn > 0.0 && (rc = enqueue_scale(s, w, 1.0 / hn))) return rc;
+      sig[j + 1] = hn > 0.0 ? 1.0 / hn : 1.0;
       // previous rotations, then the one that zeroes H(j+1, j)
       for (int i = 0; i < j; ++i) {
         const cd t = cs[i] * Hij(i, j) + sn[i] * Hij(i + 1, j);
@@ -2179,12 +2184,13 @@ int scpml_gmres(const Scpml& s, float2* x, int m, const cbs_opts* o, double beta
       for (int l = i + 1; l < k; ++l) t -= Hij(i, l) * y[l];
       y[i] = t / Hij(i, i);
     }
+    for (int i = 0; i < k; ++i) y[i] *= sig[i];
     if (k > 0) {
       HIP_TRY(hipMemcpyAsync(s.y, y.data(), k * sizeof(double2), hipMemcpyHostToDevice, p->stream));
-      if ((rc = enqueue_update(s, k, s.y, 1.0f, x))) return rc;
+      if ((rc = enqueue_update(s, k, s.y, nullptr, 1.0f, x))) return rc;
     }
     // true residual r = b - B x into V_0
-    if ((rc = enqueue_operator(s, x, s.vec(0)))) return rc;
+    if ((rc = enqueue_operator(s, x, s.vec(0), 1.0))) return rc;
     hipLaunchKernelGGL(k_gm_rsub, gg, dim3(kGmThreads), 0, p->stream, s.b, s.vec(0), s.n3);
     HIP_LAUNCHED();
     if ((rc = enqueue_dots(s, nullptr, 0, s.vec(0), s.h, true))) return rc;
@@ -2193,7 +2199,7 @@ int scpml_gmres(const Scpml& s, float2* x, int m, const cbs_opts* o, double beta
     if (!std::isfinite(beta)) return fail(CBS_E_DIVERGED, "non-finite residual after %d steps", total);
     rel = beta / beta0;
     if (rel <= o->tol || total >= o->max_iter || k == 0) break;
-    if ((rc = enqueue_scale(s, s.vec(0), 1.0 / beta))) return rc;
+    if ((rc = enqueue_scale(s, s.vec(0), 1.0 / beta, nrm))) return rc;
   }
   *iters = total;
   *rel_out = rel;

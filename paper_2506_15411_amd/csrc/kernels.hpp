@@ -51,7 +51,8 @@ enum SrcKind : int { SRC_NONE = 0, SRC_PLANE = 1, SRC_FIELD = 2, SRC_POINT = 3, 
 // stores of E_s: x pass of 192 x 192 x 256 239 us, now 228; prologue of 275 x 275
 // x 315 470, now 386).
 enum SrcForm : int { FORM_PLAIN = 0, FORM_OBLIQUE = 1, FORM_FIELD = 2 };
-// K1_RES: fout = -gamma (GW - E), the step's negative, and no forward transform
+// K1_RES: fout = -res_scale gamma (GW - E), the step's negative, and no forward
+// transform
 enum K1Mode : int { K1_FWD = 0, K1_ITER = 1, K1_INV = 2, K1_RES = 3 };
 
 constexpr int kHistCap = 1 << 16;
@@ -200,7 +201,7 @@ struct CbsArgs {
   const float2* fin;            // FIELD source / Green input
   unsigned char* rows;          // FIELD source: [3][nz][ny], 0 for rows of the field that are
                                 // all zero (written by the prologue); null: not kept
-  float2* fout;                 // Green output
+  float2* fout;                 // Green output, K1_RES output
   double* partials;             // 2 doubles per K1 block
   int k1_blocks;                // K1 or KXY blocks per illumination (partials to reduce)
   int nb;                       // illuminations advanced together (1: an ordinary solve)
@@ -219,6 +220,7 @@ struct CbsArgs {
   int green_in;                 // K1_FWD: W = fin
   int r0x, r0y, r0z;
   float src_scale;              // d^2: physical (1/m^2) sources and Green inputs
+  float res_scale;              // K1_RES
   float eps, inv_eps, kb2;      // eps d^2, 1/(eps d^2), kb^2 d^2
   float pfx, pfy, pfz;          // 2 pi / n_a
   float invN;                   // 1 / (nx ny nz)
@@ -499,7 +501,7 @@ k1_xpass(CbsArgs a) {
       sfor<0, N2>([&](auto M) {
         const float2 d = cmul(make_float2(1.0f - pv[CV(M)].y * a.inv_eps, pv[CV(M)].x * a.inv_eps),
                               csub(v[CV(M)], pe[CV(M)]));
-        a.fout[ebase + t + N1 * CV(M)] = make_float2(-d.x, -d.y);
+        a.fout[ebase + t + N1 * CV(M)] = make_float2(-a.res_scale * d.x, -a.res_scale * d.y);
       });
     }
     return;
@@ -683,7 +685,7 @@ struct XYGeom {
   static constexpr int QB = (N * N1 + THREADS - 1) / THREADS;
 };
 // MODE as in K1: K1_ITER the whole iteration, K1_FWD (W from E and the source, x
-// and y forward) and K1_RES (y and x inverse, fout = -gamma (GW - E)) its halves.
+// and y forward) and K1_RES (y and x inverse, fout = -res_scale gamma (GW - E)) its halves.
 template <int N1, int N2, int MODE, int FORM>
 __global__ void __launch_bounds__((XYGeom<N1, N2>::THREADS), (XYGeom<N1, N2>::WAVES))
 kxy_pass(CbsArgs a) {
@@ -804,7 +806,7 @@ kxy_pass(CbsArgs a) {
           const float2 v0 = pv[CV(QQ)][CV(M)];
           const float2 d = cmul(make_float2(1.0f - v0.y * a.inv_eps, v0.x * a.inv_eps),
                                 csub(v[CV(M)], pe[CV(QQ)][CV(M)]));
-          a.fout[ebase + o + N1 * CV(M)] = make_float2(-d.x, -d.y);
+          a.fout[ebase + o + N1 * CV(M)] = make_float2(-a.res_scale * d.x, -a.res_scale * d.y);
         });
         return;
       }

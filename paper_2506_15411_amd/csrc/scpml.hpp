@@ -143,8 +143,8 @@ k_gm_dots_finish(const double2* part, int nblk, double2* h) {
   if (threadIdx.x == 0) h[blockIdx.x] = r;
 }
 
-// w += sign sum_{i < cnt} c_i V_i, coefficients c (FP64) in device memory; with
-// part, part[blk] is a partial of |w|^2 after the update (a sweep over w of its
+// w += sign sum_{i < cnt} c_i / nrm_i V_i, coefficients c (FP64) and squared norms
+// nrm (null: 1) in device memory; with part, part[blk] is a partial of |w|^2 after the update (a sweep over w of its
 // own before).  Vectors are added in order; a work-group takes 16 KB pieces of
 // each, two vectors' loads in flight together: 2.60 ms a step on average over a
 // GMRES(40) cycle of 275 x 275 x 315 (4.9 TB/s), element by element 2.70 with
@@ -152,12 +152,14 @@ k_gm_dots_finish(const double2* part, int nblk, double2* h) {
 constexpr int kGmUpdateBlocks = 2048;
 static_assert(kGmUpdateBlocks <= (kScpmlMaxRestart + 1) * kGmBlocks, "partials fit");
 __global__ void __launch_bounds__(kGmThreads)
-k_gm_update(const float2* V, long long vstride, int cnt, const double2* c, float sign,
-            float2* w, long long n, double2* part) {
+k_gm_update(const float2* V, long long vstride, int cnt, const double2* c, const double2* nrm,
+            float sign, float2* w, long long n, double2* part) {
   __shared__ float2 cf[kScpmlMaxRestart + 1];
   __shared__ double2 red[kGmThreads / 64];
-  if (threadIdx.x < cnt)
-    cf[threadIdx.x] = make_float2((float)(sign * c[threadIdx.x].x), (float)(sign * c[threadIdx.x].y));
+  if (threadIdx.x < cnt) {
+    const double f = nrm ? sign / nrm[threadIdx.x].x : sign;
+    cf[threadIdx.x] = make_float2((float)(f * c[threadIdx.x].x), (float)(f * c[threadIdx.x].y));
+  }
   __syncthreads();
   double s2 = 0.0;
   constexpr int E = 8, G = 2;   // elements of a thread, vectors in flight
@@ -204,8 +206,9 @@ k_gm_update(const float2* V, long long vstride, int cnt, const double2* c, float
   }
 }
 
-// w = s w
-__global__ void k_gm_scale(float2* w, long long n, float s) {
+// w = s w, a unit vector: *nrm = 1
+__global__ void k_gm_scale(float2* w, long long n, float s, double2* nrm) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *nrm = make_double2(1.0, 0.0);
   for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n;
        e += (long long)gridDim.x * blockDim.x) {
     const float2 v = w[e];
