@@ -13,8 +13,8 @@
 // registers of the level-B threads and every level writes where it read.
 // Vector work bounds them (five transforms per 104 bytes moved); components are
 // separate work-groups, since a loop over them keeps the tables of all three in
-// registers.  The operator at 275 x 275 x 315 takes 2.75 ms, dense matrix products
-// on the FP32 matrix cores 7.04 ms; at 64^3 90 us against 460; relative error
+// registers.  The operator at 275 x 275 x 315 takes 2.54 ms, dense matrix products
+// on the FP32 matrix cores 7.04 ms; at 64^3 89 us against 460; relative error
 // against FP64 2.0e-7 (6.4e-7) on noise and 3.0e-6 (2.6e-6) on a spherical wave at
 // lambda / 16.
 #pragma once
@@ -88,8 +88,29 @@ __device__ __forceinline__ float sc_freq(int k, bool t) {
 }
 __device__ __forceinline__ float2 imul(float q, float2 v) { return make_float2(-q * v.y, q * v.x); }
 
+// A layer of at most N2 voxels a side holds elements j2 + N2 q of a level-A task
+// for q = 0 and q = N1 - 1 alone (THIN): what lambda multiplies is needed there
+// only, and lambda D v is zero elsewhere.  The inverse DFT-N1 for those two
+// outputs, and the forward one of those two inputs, are sums of N1 terms, a third
+// of the work of a DFT-25 (275 x 275 x 315, layers of 8: x axis 630 -> 457 us, y
+// axis 760 -> 573; four edge elements or more a side would cost what the full
+// transform does, the 48-voxel z layer keeps it).
+template <int N1>
+__device__ __forceinline__ void edge_out(const float2* b, float2& o0, float2& o1) {
+  o0 = o1 = b[0];
+  sfor<1, N1>([&](auto K) {
+    o0 = cadd(o0, b[CV(K)]);
+    o1 = cadd(o1, rot<N1, -CV(K)>(b[CV(K)]));
+  });
+}
+template <int N1>
+__device__ __forceinline__ void edge_in(float2 i0, float2 i1, float2* b) {
+  sfor<0, N1>([&](auto K) { b[CV(K)] = cadd(i0, rot<N1, CV(K)>(i1)); });
+}
+constexpr bool sc_thin(int n1, int n2, int p) { return n1 >= 5 && p <= n2; }
+
 // F_c (+)= alpha [A v_c for c != axis, B v_c for c = axis], u_axis = T v_axis
-template <int N1, int N2, bool ROW>
+template <int N1, int N2, bool ROW, bool THIN>
 __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_apply(ScAxis a) {
   using G = ScGeom<N1, N2, ROW>;
   constexpr int N = G::N, TX = G::TX, T = G::THREADS;
@@ -151,12 +172,28 @@ __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_apply(ScAxi
   if (oka) {
     float2 b[N1];
     sfor<0, N1>([&](auto K) { b[CV(K)] = cmulc(l1[pa + N2 * SP * CV(K)], twt[CV(K)]); });
-    dft<N1, +1>(b);   // D v (T v) at j2 + N2 q
+    float2 e0, e1;
+    if (!THIN || own) {
+      dft<N1, +1>(b);   // D v (T v) at j2 + N2 q
+      e0 = b[0];
+      e1 = b[N1 - 1];
+    } else {
+      edge_out<N1>(b, e0, e1);
+    }
     if (own) {
       float2* u = a.u + c * nvox;
       sfor<0, N1>([&](auto J) { sc_at(u, g0 + CV(J) * gs) = b[CV(J)]; });
     }
-    if (a.p > 0) {
+    if (THIN && a.p > 0) {
+      const float2 s0 = si[j2], s1 = si[j2 + N2 * (N1 - 1)];
+      const float2 m0 = make_float2(1.0f - s0.x, -s0.y), m1 = make_float2(1.0f - s1.x, -s1.y);
+      edge_in<N1>(cmul(m0, e0), cmul(m1, e1), b);
+      sfor<0, N1>([&](auto K) { l1[pa + N2 * SP * CV(K)] = cmul(b[CV(K)], twt[CV(K)]); });
+      sfor<0, N1>([&](auto K) { b[CV(K)] = cmulc(l2[pa + N2 * SP * CV(K)], twt[CV(K)]); });
+      edge_out<N1>(b, e0, e1);
+      l2[pa] = cmul(m0, e0);
+      l2[pa + N2 * SP * (N1 - 1)] = cmul(m1, e1);
+    } else if (a.p > 0) {
       sfor<0, N1>([&](auto J) {
         const float2 s = si[j2 + N2 * CV(J)];
         b[CV(J)] = cmul(make_float2(1.0f - s.x, -s.y), b[CV(J)]);
@@ -195,7 +232,9 @@ __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_apply(ScAxi
     sfor<0, N1>([&](auto K) { b[CV(K)] = cmulc(l1[pa + N2 * SP * CV(K)], twt[CV(K)]); });
     dft<N1, +1>(b);
     sfor<0, N1>([&](auto J) {
-      const float2 w = cadd(l2[pa + N2 * SP * CV(J)], cmul(si[j2 + N2 * CV(J)], b[CV(J)]));
+      constexpr bool IN = !THIN || CV(J) == 0 || CV(J) == N1 - 1;   // in the layer
+      float2 w = b[CV(J)];
+      if constexpr (IN) w = cadd(l2[pa + N2 * SP * CV(J)], cmul(si[j2 + N2 * CV(J)], w));
       sc_at(F, g0 + CV(J) * gs) = make_float2(f[CV(J)].x + a.alpha * w.x, f[CV(J)].y + a.alpha * w.y);
     });
   }
@@ -220,7 +259,7 @@ static __global__ void __launch_bounds__(256) sc_combine(ScAxis a) {
 }
 
 // F_axis += alpha [T Z + (s^-1 - 1) T X] with X and Z of sc_combine
-template <int N1, int N2, bool ROW>
+template <int N1, int N2, bool ROW, bool THIN>
 __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_grad(ScAxis a) {
   using G = ScGeom<N1, N2, ROW>;
   constexpr int N = G::N, TX = G::TX, T = G::THREADS;
@@ -279,8 +318,16 @@ __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_grad(ScAxis
   if (oka) {
     if (layer) {
       sfor<0, N1>([&](auto K) { z[CV(K)] = cmulc(l2[pa + N2 * SP * CV(K)], twt[CV(K)]); });
-      dft<N1, +1>(z);
+      if constexpr (THIN) {
+        float2 e0, e1;
+        edge_out<N1>(z, e0, e1);
+        z[0] = e0;
+        z[N1 - 1] = e1;
+      } else {
+        dft<N1, +1>(z);
+      }
       sfor<0, N1>([&](auto J) {
+        if constexpr (THIN && CV(J) != 0 && CV(J) != N1 - 1) return;
         const float2 s = si[j2 + N2 * CV(J)];
         const float2 w = cmul(make_float2(s.x - 1.0f, s.y), z[CV(J)]);
         f[CV(J)] = make_float2(f[CV(J)].x + a.alpha * w.x, f[CV(J)].y + a.alpha * w.y);
@@ -301,10 +348,18 @@ void launch_sc(const ScAxis& a, bool grad, hipStream_t s) {
   using G = ScGeom<N1, N2, ROW>;
   const long long tiles = ROW ? ((long long)a.ny * a.nz + G::TX - 1) / G::TX
                               : (long long)((a.nx + G::TX - 1) / G::TX) * (a.axis == 1 ? a.nz : a.ny);
-  if (grad)
-    hipLaunchKernelGGL((sc_grad<N1, N2, ROW>), dim3((unsigned)tiles), dim3(G::THREADS), 0, s, a);
-  else
-    hipLaunchKernelGGL((sc_apply<N1, N2, ROW>), dim3(3u * (unsigned)tiles), dim3(G::THREADS), 0, s, a);
+  auto go = [&](auto thin) {
+    constexpr bool THIN = CV(thin);
+    if (grad)
+      hipLaunchKernelGGL((sc_grad<N1, N2, ROW, THIN>), dim3((unsigned)tiles), dim3(G::THREADS), 0, s, a);
+    else
+      hipLaunchKernelGGL((sc_apply<N1, N2, ROW, THIN>), dim3(3u * (unsigned)tiles),
+                         dim3(G::THREADS), 0, s, a);
+  };
+  if constexpr (sc_thin(N1, N2, 0)) {
+    if (sc_thin(N1, N2, a.p)) return go(std::true_type{});
+  }
+  go(std::false_type{});
 }
 
 }  // namespace cbs

@@ -39,3 +39,23 @@ def test_every_length_on_every_axis(n, device):
             err = float(np.linalg.norm(out - ref) / np.linalg.norm(ref))
             assert err < 2e-6, (shape, pml, order, err)
             p.close()
+
+
+# layers one voxel below, at and one above the length (N2 = 8, 9, 10, 11, 23) up to
+# which the transforms form the layer's elements alone
+@pytest.mark.parametrize("n,p", [(64, 7), (64, 8), (64, 9), (189, 8), (189, 9), (189, 10),
+                                 (100, 9), (100, 10), (100, 11), (275, 1), (275, 10), (275, 11),
+                                 (275, 12), (621, 22), (621, 23), (621, 24)])
+def test_layers_around_the_edge_form(n, p, device):
+    for shape in [(n, 3, 5), (9, n, 2)] + ([(5, 3, n)] if n != 621 else []):
+        pml = tuple(p if m == n else 0 for m in shape)
+        g = oc.Grid(*shape, LAM / 8, LAM, 1.0, pml, sigma_max=0.0)
+        rng = np.random.default_rng(n + p)
+        v = (rng.standard_normal((3,) + g.vshape)
+             + 1j * rng.standard_normal((3,) + g.vshape)).astype(np.complex64)
+        q = Plan(shape, LAM / 8, LAM, 1.0, pml, device=device, sigma_max=0.0)
+        out = q.scpml_operator(torch.from_numpy(v).to(device), 0.75, 2).cpu().numpy()
+        ref = scpml.delta_apply(g, v.astype(np.complex128), 0.75, 2)
+        err = float(np.linalg.norm(out - ref) / np.linalg.norm(ref))
+        assert err < 2e-6, (shape, pml, err)
+        q.close()
