@@ -918,6 +918,17 @@ void set_illuminations(const cbs_plan_s* p, CbsArgs& a, int nb) {
   a.k1_blocks = a.fused ? 3 * p->nz : p->k1_blocks;
 }
 
+// Grids on which a stopped solve's remaining launches cost more than the latency
+// they hide: their passes look at the stop flag before they load anything, and a
+// blocking solve keeps one quantum in flight instead of two.  A solve in us, small
+// form -> large form, to 1e-4 and for 40 iterations (quanta of 10): 64^3 3355 ->
+// 3482, 873 -> 913; 121 x 189 x 100 45700 -> 46110, 4125 -> 4210; 189 x 189 x 121
+// 154820 -> 155540, 7165 -> 7220; 192 x 192 x 256 179340 -> 178070, 17350 -> 17430;
+// 275 x 275 x 315 636170 -> 631700, 48620 -> 48720.
+bool large_grid(const cbs_plan_s* p) {
+  return (long long)p->nx * p->ny * p->nz > 6LL << 20;
+}
+
 CbsArgs base_args(cbs_plan_s* p) {
   CbsArgs a;
   std::memset(&a, 0, sizeof(a));
@@ -956,6 +967,7 @@ CbsArgs base_args(cbs_plan_s* p) {
   a.pfz = (float)(2.0 * M_PI / p->nz);
   a.invN = (float)(1.0 / ((double)p->nx * p->ny * p->nz));
   a.src_scale = (float)d2;
+  a.flag_first = large_grid(p) ? 1 : 0;
   return a;
 }
 
@@ -1154,16 +1166,17 @@ int end_solve(cbs_plan_s* p, cbs_stats* stats) {
 }
 
 // Blocking solve on top of the primitives: quanta of check_every iterations, two
-// of them in flight, so the device has work while the host reads the state of
-// the one before (a 64^3 iteration takes 20 us and a host round trip about as
-// long: 100 iterations 2.13 -> 2.05 ms, 40 iterations of 32^3 0.54 -> 0.51).  A
-// solve that meets tol leaves at most the
-// second quantum's launches, which return at entry.
+// of them in flight (one on large grids), so the device has work while the host
+// reads the state of the one before (a 64^3 iteration takes 20 us and a host
+// round trip about as long: 100 iterations 2.13 -> 2.05 ms, 40 iterations of 32^3
+// 0.54 -> 0.51).  A solve that meets tol leaves at most the second quantum's
+// launches, which return before they compute or write.
 int run_blocking(cbs_plan_s* p, int check_every, cbs_stats* stats) {
   auto& A = p->act;
+  const int ahead = large_grid(p) ? 1 : 2;
   int done = 0, rc = CBS_OK;
   while (!done) {
-    while (!rc && A.count < 2 && A.enqueued < A.max_iter) rc = advance_solve(p, check_every);
+    while (!rc && A.count < ahead && A.enqueued < A.max_iter) rc = advance_solve(p, check_every);
     if (!rc && A.count == 0) rc = fail(CBS_E_STATE, "the device did not stop at max_iter");
     if (rc) break;
     const hipError_t e = hipEventSynchronize(p->evq[A.head]);

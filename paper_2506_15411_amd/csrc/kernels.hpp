@@ -213,6 +213,7 @@ struct CbsArgs {
   int oblique;                  // some illumination has kx or ky != 0 (phx, phy not all 1)
   int k1_prio;                  // x-pass: raise wave priority for the load phase (set by launch_k1)
   int ky_prio;                  // y pass: the same (set by launch_ky)
+  int flag_first;               // wait for the stop flag before the first loads (large grids)
   double* hist;                 // residual history
   DevState* st;
   int src;                      // SrcKind
@@ -388,6 +389,7 @@ k1_xpass(CbsArgs a) {
   __shared__ double red[2 * (G::THREADS / 64)];
 
   const int done = MODE == K1_ITER ? a.st->done : 0;
+  if (a.flag_first && done) return;
   const int tid = threadIdx.x;
   // with few waves per SIMD, a work-group's load phase would otherwise wait
   // behind the other waves' vector work
@@ -590,6 +592,7 @@ ky_pass(CbsArgs a) {
   __shared__ float2 lds[N * TX];
   __shared__ float2 tw[N];
   const int done = a.st->done;
+  if (a.flag_first && done) return;
   const int tid = threadIdx.x;
   if (a.ky_prio) __builtin_amdgcn_s_setprio(kLoadPrio);
   TwStage<N, G::THREADS> tws;
@@ -695,6 +698,7 @@ kxy_pass(CbsArgs a) {
   __shared__ float2 tw[N];
   __shared__ double red[2 * (T / 64)];
   const int done = MODE == K1_ITER ? a.st->done : 0;
+  if (a.flag_first && done) return;
   const int tid = threadIdx.x;
   TwStage<N, T> tws;
   tws.issue(a.twx, tid);
@@ -723,9 +727,9 @@ kxy_pass(CbsArgs a) {
         sfor<0, N1>([&](auto J) { b[CV(QQ)][CV(J)] = w[N2 * kBrick * CV(J)]; });
       }
     });
-    // The stop flag, read first, is waited for behind the issued loads, here and in
-    // the other passes: one round trip less per launch (16^3 iteration 8.5 -> 7.9
-    // us, 32^3 10.9 -> 10.1, 64^3 19.5 -> 19.1, 275 x 275 x 315 1200 -> 1194).
+    // On small grids (flag_first 0) the stop flag, read first, is waited for behind
+    // the issued loads, here and in the other passes: one round trip less per launch
+    // (16^3 iteration 8.5 -> 7.9 us, 32^3 10.9 -> 10.1, 64^3 19.5 -> 19.1).
     asm volatile("" ::: "memory");
     if (done) return;
     tws.commit(tw, tid);
@@ -921,6 +925,7 @@ kz_pass(CbsArgs a) {
     if (threadIdx.x == 0) a.st->pending = 0;
     return;
   }
+  if (a.flag_first && done) return;
   const int tid = threadIdx.x;
   TwStage<N, G::THREADS> tws;
   tws.issue(a.twz, tid);
