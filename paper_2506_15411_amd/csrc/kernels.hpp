@@ -319,9 +319,10 @@ __device__ __forceinline__ unsigned xcd_remap(unsigned b, unsigned total) {
   return k * q + (k < r ? k : r) + j;
 }
 
-// The stop flag before the first loads, on large grids.  A load of its own: waiting
-// for flag_first would wait for the flag too if that were already in flight (64^3
-// iteration 19.1 -> 19.7 us).
+// The stop flag before the first loads, on large grids: in the x and y passes, not
+// in the z and plane passes, which the smallest grids run (64^3 iteration with the
+// test 19.7 us, without 19.1).  A load of its own: waiting for flag_first would
+// wait for the flag too if that were already in flight.
 __device__ __forceinline__ bool stop_first(const CbsArgs& a) {
   const bool stop = a.flag_first && a.st->done;
   asm volatile("" ::: "memory");
@@ -706,7 +707,6 @@ kxy_pass(CbsArgs a) {
   __shared__ float2 lds[N * P];
   __shared__ float2 tw[N];
   __shared__ double red[2 * (T / 64)];
-  if (MODE == K1_ITER && stop_first(a)) return;
   const int done = MODE == K1_ITER ? a.st->done : 0;
   const int tid = threadIdx.x;
   TwStage<N, T> tws;
@@ -917,7 +917,6 @@ kz_pass(CbsArgs a) {
   constexpr int N = G::N;
   __shared__ float2 lds[3 * N * TX];
   __shared__ float2 tw[N];
-  if (stop_first(a)) return;
   const int done = a.st->done;
   // block 0 transforms nothing: it finishes the previous iteration's residual
   // (stream order: the x pass that wrote the partials has completed) beside the
