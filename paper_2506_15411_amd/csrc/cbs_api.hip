@@ -2114,6 +2114,11 @@ int read_back(cbs_plan_s* p, const double2* dev, std::complex<double>* host, int
   return CBS_OK;
 }
 
+// |w| from the sum of its squares.  A NaN stays one and is refused by the caller's
+// finiteness test (std::max(0.0, NaN) is 0: a vector that overflowed would read as
+// a residual of zero).
+double norm_of(double sq) { return sq < 0.0 ? 0.0 : std::sqrt(sq); }
+
 // Restarted GMRES(m) on B x = b from x = 0 (x in E_dev).  Arnoldi with
 // classical Gram-Schmidt (fused dot and update passes over the basis),
 // repeated for a step whose projection shortened w more than tenfold;
@@ -2164,7 +2169,7 @@ int scpml_gmres(const Scpml& s, float2* x, int m, const cbs_opts* o, double beta
         for (int i = 0; i <= j; ++i) Hij(i, j) += sig[i] * hv[(m + 1) + i];
         nn = hv[2 * (m + 1) + j + 1].real();
       }
-      const double hn = std::sqrt(std::max(0.0, nn));
+      const double hn = norm_of(nn);
       Hij(j + 1, j) = hn;
       for (int i = 0; i <= j; ++i)
         if (!std::isfinite(Hij(i, j).real()) || !std::isfinite(Hij(i, j).imag()))
@@ -2208,7 +2213,7 @@ int scpml_gmres(const Scpml& s, float2* x, int m, const cbs_opts* o, double beta
     HIP_LAUNCHED();
     if ((rc = enqueue_dots(s, nullptr, 0, s.vec(0), s.h, true))) return rc;
     if ((rc = read_back(p, s.h, hv.data(), 1))) return rc;   // also retires the y upload
-    beta = std::sqrt(std::max(0.0, hv[0].real()));
+    beta = norm_of(hv[0].real());
     if (!std::isfinite(beta)) return fail(CBS_E_DIVERGED, "non-finite residual after %d steps", total);
     rel = beta / beta0;
     if (rel <= o->tol || total >= o->max_iter || k == 0) break;
@@ -2278,7 +2283,7 @@ int cbs_solve_scpml(cbs_plan_t p, const cbs_source* src, void* E_dev, const cbs_
   std::complex<double> bb;
   if ((rc = enqueue_dots(s, nullptr, 0, s.b, s.h, true))) return rc;
   if ((rc = read_back(p, s.h, &bb, 1))) return rc;
-  const double beta0 = std::sqrt(std::max(0.0, bb.real()));
+  const double beta0 = norm_of(bb.real());
   if (!std::isfinite(beta0)) return fail(CBS_E_DIVERGED, "non-finite source");
   std::vector<double> hist;
   int iters = 0;
