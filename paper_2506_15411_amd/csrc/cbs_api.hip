@@ -1942,7 +1942,7 @@ bool scpml_layout(int nx, int ny, int nz, int restart, ScpmlLayout& S) {
   S.b = take(3 * N * sizeof(float2));
   S.F = take(3 * N * sizeof(float2));
   S.u = take(3 * N * sizeof(float2));
-  for (int a = 0; a < 3; ++a) S.sinv[a] = take((size_t)dims[a] * sizeof(float2));
+  for (int a = 0; a < 3; ++a) S.sinv[a] = take((size_t)2 * dims[a] * sizeof(float2));   // 1/s, lambda
   S.part = take((size_t)(kScpmlMaxRestart + 1) * kGmBlocks * sizeof(double2));
   S.h = take((size_t)3 * (kScpmlMaxRestart + 1) * sizeof(double2));
   S.y = take((size_t)(kScpmlMaxRestart + 1) * sizeof(double2));
@@ -1955,7 +1955,7 @@ struct Scpml {
   int dims[3];
   long long N, n3;            // voxels; complex values of a vector field
   float2 *basis, *b, *F, *u;
-  const float2* sinv[3];      // 1/s along each axis
+  const float2 *sinv[3], *lam[3];   // 1/s and 1 - 1/s along each axis
   double2 *part, *h, *y;
   float2* vec(int i) const { return basis + (long long)i * n3; }
 };
@@ -1993,8 +1993,9 @@ int scpml_setup(cbs_plan_s* p, const cbs_scpml* layer, int restart, void* work, 
     const int n = s.dims[a];
     float2* si = reinterpret_cast<float2*>(base + S.sinv[a]);
     s.sinv[a] = si;
-    hipLaunchKernelGGL(k_scpml_sinv, dim3((n + 127) / 128), dim3(128), 0, p->stream, n, p->pml[a],
-                       layer->order, layer->alpha_max, si);
+    s.lam[a] = si + n;
+    hipLaunchKernelGGL(k_scpml_stretch, dim3((n + 127) / 128), dim3(128), 0, p->stream, n, p->pml[a],
+                       layer->order, layer->alpha_max, si, si + n);
     HIP_LAUNCHED();
   }
   return CBS_OK;
@@ -2015,7 +2016,10 @@ int enqueue_delta(const Scpml& s, const float2* v, float2* F, float alpha) {
   a.v = v;
   a.F = F;
   a.u = s.u;
-  for (int b = 0; b < 3; ++b) a.sinv3[b] = s.sinv[b];
+  for (int b = 0; b < 3; ++b) {
+    a.sinv3[b] = s.sinv[b];
+    a.lam3[b] = s.lam[b];
+  }
   a.nx = p->nx;
   a.ny = p->ny;
   a.nz = p->nz;
@@ -2033,7 +2037,6 @@ int enqueue_delta(const Scpml& s, const float2* v, float2* F, float alpha) {
       a.axis = b;
       a.first = b == 0 ? 1 : 0;
       a.p = p->pml[b];
-      a.sinv = s.sinv[b];
       a.tw = tw[b];
       launch[b](a, grad != 0, p->stream);
       HIP_LAUNCHED();

@@ -50,15 +50,19 @@ __device__ __forceinline__ double stretch_depth(int i, int n, int p) {
   return 0.0;
 }
 
-// 1/s over an axis (FP64 rounded to FP32), one thread per voxel
-__global__ void k_scpml_sinv(int n, int pml, int order, double alpha, float2* sinv) {
+// 1/s and lambda = 1 - 1/s over an axis (each FP64 rounded to FP32 once: 1 minus the
+// rounded 1/s loses the real part of a small lambda, 6e-8 of 1, whole at a depth
+// where a^2 is less), one thread per voxel
+__global__ void k_scpml_stretch(int n, int pml, int order, double alpha, float2* sinv, float2* lam) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= n) return;
   const double u = stretch_depth(m, n, pml);
   double um = 1.0;
   for (int k = 0; k < order; ++k) um *= u;
   const double a = alpha * um;   // s = 1 + i a, 1/s = (1 - i a) / (1 + a^2)
-  sinv[m] = make_float2((float)(1.0 / (1.0 + a * a)), (float)(-a / (1.0 + a * a)));
+  const double r = 1.0 / (1.0 + a * a);
+  sinv[m] = make_float2((float)r, (float)(-a * r));
+  lam[m] = make_float2((float)(a * a * r), (float)(a * r));
 }
 
 // ---------------------------------------------------------------------------

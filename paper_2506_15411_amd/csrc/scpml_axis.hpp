@@ -25,8 +25,7 @@ struct ScAxis {
   const float2* v;      // phase 1: the field [3][nz][ny][nx]
   float2* F;            // result [3][nz][ny][nx]
   float2* u;            // T_b v_b of every axis b, [3][nz][ny][nx]
-  const float2* sinv;   // 1/s along the axis
-  const float2* sinv3[3];   // 1/s along x, y and z
+  const float2 *sinv3[3], *lam3[3];   // 1/s and lambda = 1 - 1/s along x, y and z
   const float2* tw;     // the axis's twiddle table
   int nx, ny, nz;
   int axis;             // 0 = x, 1 = y, 2 = z
@@ -115,11 +114,11 @@ __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_apply(ScAxi
   using G = ScGeom<N1, N2, ROW>;
   constexpr int N = G::N, TX = G::TX, T = G::THREADS;
   __shared__ float2 l1[G::SIZE], l2[G::SIZE];
-  __shared__ float2 tw[N], si[N];
+  __shared__ float2 tw[N], lam[N];
   const int tid = threadIdx.x;
   for (int i = tid; i < N; i += T) {
     tw[i] = a.tw[i];
-    si[i] = a.sinv[i];
+    lam[i] = a.lam3[a.axis][i];
   }
   const int la = ROW ? tid / N2 : tid % TX, j2 = ROW ? tid % N2 : tid / TX;
   const int lb = ROW ? tid / N1 : tid % TX, k1 = ROW ? tid % N1 : tid / TX;
@@ -185,28 +184,21 @@ __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_apply(ScAxi
       sfor<0, N1>([&](auto J) { sc_at(u, g0 + CV(J) * gs) = b[CV(J)]; });
     }
     if (THIN && a.p > 0) {
-      const float2 s0 = si[j2], s1 = si[j2 + N2 * (N1 - 1)];
-      const float2 m0 = make_float2(1.0f - s0.x, -s0.y), m1 = make_float2(1.0f - s1.x, -s1.y);
+      const float2 m0 = lam[j2], m1 = lam[j2 + N2 * (N1 - 1)];
       edge_in<N1>(cmul(m0, e0), cmul(m1, e1), b);
       sfor<0, N1>([&](auto K) { l1[pa + N2 * SP * CV(K)] = cmul(b[CV(K)], twt[CV(K)]); });
       sfor<0, N1>([&](auto K) { b[CV(K)] = cmulc(l2[pa + N2 * SP * CV(K)], twt[CV(K)]); });
       edge_out<N1>(b, e0, e1);
-      l2[pa] = cmul(m0, e0);
-      l2[pa + N2 * SP * (N1 - 1)] = cmul(m1, e1);
+      l2[pa] = e0;
+      l2[pa + N2 * SP * (N1 - 1)] = e1;
     } else if (a.p > 0) {
-      sfor<0, N1>([&](auto J) {
-        const float2 s = si[j2 + N2 * CV(J)];
-        b[CV(J)] = cmul(make_float2(1.0f - s.x, -s.y), b[CV(J)]);
-      });
+      sfor<0, N1>([&](auto J) { b[CV(J)] = cmul(lam[j2 + N2 * CV(J)], b[CV(J)]); });
       dft<N1, -1>(b);
       sfor<0, N1>([&](auto K) { l1[pa + N2 * SP * CV(K)] = cmul(b[CV(K)], twt[CV(K)]); });
-      // lambda D^2 v waits in l2, at this task's own positions
+      // D^2 v waits in l2, at this task's own positions
       sfor<0, N1>([&](auto K) { b[CV(K)] = cmulc(l2[pa + N2 * SP * CV(K)], twt[CV(K)]); });
       dft<N1, +1>(b);
-      sfor<0, N1>([&](auto J) {
-        const float2 s = si[j2 + N2 * CV(J)];
-        l2[pa + N2 * SP * CV(J)] = cmul(make_float2(1.0f - s.x, -s.y), b[CV(J)]);
-      });
+      sfor<0, N1>([&](auto J) { l2[pa + N2 * SP * CV(J)] = b[CV(J)]; });
     } else if (a.first) {   // own component without a layer: B = 0
       sfor<0, N1>([&](auto J) { sc_at(F, g0 + CV(J) * gs) = make_float2(0.f, 0.f); });
     }
@@ -234,13 +226,14 @@ __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_apply(ScAxi
     sfor<0, N1>([&](auto J) {
       constexpr bool IN = !THIN || CV(J) == 0 || CV(J) == N1 - 1;   // in the layer
       float2 w = b[CV(J)];
-      if constexpr (IN) w = cadd(l2[pa + N2 * SP * CV(J)], cmul(si[j2 + N2 * CV(J)], w));
+      // lambda D^2 v + s^-1 w with s^-1 = 1 - lambda
+      if constexpr (IN) w = cadd(w, cmul(lam[j2 + N2 * CV(J)], csub(l2[pa + N2 * SP * CV(J)], w)));
       sc_at(F, g0 + CV(J) * gs) = make_float2(f[CV(J)].x + a.alpha * w.x, f[CV(J)].y + a.alpha * w.y);
     });
   }
 }
 
-// X = sum_b s_b^-1 u_b and Z = sum_b (s_b^-1 - 1) u_b, in place of u_x and u_y.
+// X = sum_b s_b^-1 u_b and Z = sum_b (s_b^-1 - 1) u_b = -sum_b lambda_b u_b, in place of u_x and u_y.
 // A launch of its own: accumulated in sc_apply X and Z would be read and written
 // by every axis, and formed in sc_grad from three fields they cost it its
 // occupancy (256 registers; 586 us against 246 for the x axis of 275 x 275 x 315).
@@ -252,9 +245,8 @@ static __global__ void __launch_bounds__(256) sc_combine(ScAxis a) {
     const float2 v0 = u0[i], v1 = u1[i], v2 = u2[i];
     const float2 s0 = a.sinv3[0][x], s1 = a.sinv3[1][y], s2 = a.sinv3[2][z];
     u0[i] = cadd(cmul(s0, v0), cadd(cmul(s1, v1), cmul(s2, v2)));
-    u1[i] = cadd(cmul(make_float2(s0.x - 1.0f, s0.y), v0),
-                 cadd(cmul(make_float2(s1.x - 1.0f, s1.y), v1),
-                      cmul(make_float2(s2.x - 1.0f, s2.y), v2)));
+    const float2 m0 = a.lam3[0][x], m1 = a.lam3[1][y], m2 = a.lam3[2][z];
+    u1[i] = cscale(cadd(cmul(m0, v0), cadd(cmul(m1, v1), cmul(m2, v2))), -1.0f);
   }
 }
 
@@ -264,11 +256,11 @@ __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_grad(ScAxis
   using G = ScGeom<N1, N2, ROW>;
   constexpr int N = G::N, TX = G::TX, T = G::THREADS;
   __shared__ float2 l1[G::SIZE], l2[G::SIZE];
-  __shared__ float2 tw[N], si[N];
+  __shared__ float2 tw[N], lam[N];
   const int tid = threadIdx.x;
   for (int i = tid; i < N; i += T) {
     tw[i] = a.tw[i];
-    si[i] = a.sinv[i];
+    lam[i] = a.lam3[a.axis][i];
   }
   const int la = ROW ? tid / N2 : tid % TX, j2 = ROW ? tid % N2 : tid / TX;
   const int lb = ROW ? tid / N1 : tid % TX, k1 = ROW ? tid % N1 : tid / TX;
@@ -328,9 +320,8 @@ __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_grad(ScAxis
       }
       sfor<0, N1>([&](auto J) {
         if constexpr (THIN && CV(J) != 0 && CV(J) != N1 - 1) return;
-        const float2 s = si[j2 + N2 * CV(J)];
-        const float2 w = cmul(make_float2(s.x - 1.0f, s.y), z[CV(J)]);
-        f[CV(J)] = make_float2(f[CV(J)].x + a.alpha * w.x, f[CV(J)].y + a.alpha * w.y);
+        const float2 w = cmul(lam[j2 + N2 * CV(J)], z[CV(J)]);   // s^-1 - 1 = -lambda
+        f[CV(J)] = make_float2(f[CV(J)].x - a.alpha * w.x, f[CV(J)].y - a.alpha * w.y);
       });
     }
     sfor<0, N1>([&](auto K) { z[CV(K)] = cmulc(l1[pa + N2 * SP * CV(K)], twt[CV(K)]); });
