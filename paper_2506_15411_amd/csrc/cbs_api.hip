@@ -1923,7 +1923,7 @@ int cbs_bandwidth_probe(const void* src, void* dst, size_t bytes, int reps, void
 namespace {
 
 struct ScpmlLayout {
-  size_t basis, b, F, u, sinv[3], part, h, y, total;
+  size_t basis, b, F, u, lam[3], part, h, y, total;
 };
 
 bool scpml_layout(int nx, int ny, int nz, int restart, ScpmlLayout& S) {
@@ -1942,7 +1942,7 @@ bool scpml_layout(int nx, int ny, int nz, int restart, ScpmlLayout& S) {
   S.b = take(3 * N * sizeof(float2));
   S.F = take(3 * N * sizeof(float2));
   S.u = take(3 * N * sizeof(float2));
-  for (int a = 0; a < 3; ++a) S.sinv[a] = take((size_t)2 * dims[a] * sizeof(float2));   // 1/s, lambda
+  for (int a = 0; a < 3; ++a) S.lam[a] = take((size_t)dims[a] * sizeof(float2));
   S.part = take((size_t)(kScpmlMaxRestart + 1) * kGmBlocks * sizeof(double2));
   S.h = take((size_t)3 * (kScpmlMaxRestart + 1) * sizeof(double2));
   S.y = take((size_t)(kScpmlMaxRestart + 1) * sizeof(double2));
@@ -1955,7 +1955,7 @@ struct Scpml {
   int dims[3];
   long long N, n3;            // voxels; complex values of a vector field
   float2 *basis, *b, *F, *u;
-  const float2 *sinv[3], *lam[3];   // 1/s and 1 - 1/s along each axis
+  const float2* lam[3];       // 1 - 1/s along each axis
   double2 *part, *h, *y;
   float2* vec(int i) const { return basis + (long long)i * n3; }
 };
@@ -1991,11 +1991,10 @@ int scpml_setup(cbs_plan_s* p, const cbs_scpml* layer, int restart, void* work, 
   s.y = reinterpret_cast<double2*>(base + S.y);
   for (int a = 0; a < 3; ++a) {
     const int n = s.dims[a];
-    float2* si = reinterpret_cast<float2*>(base + S.sinv[a]);
-    s.sinv[a] = si;
-    s.lam[a] = si + n;
-    hipLaunchKernelGGL(k_scpml_stretch, dim3((n + 127) / 128), dim3(128), 0, p->stream, n, p->pml[a],
-                       layer->order, layer->alpha_max, si, si + n);
+    float2* lam = reinterpret_cast<float2*>(base + S.lam[a]);
+    s.lam[a] = lam;
+    hipLaunchKernelGGL(k_scpml_lambda, dim3((n + 127) / 128), dim3(128), 0, p->stream, n, p->pml[a],
+                       layer->order, layer->alpha_max, lam);
     HIP_LAUNCHED();
   }
   return CBS_OK;
@@ -2016,10 +2015,7 @@ int enqueue_delta(const Scpml& s, const float2* v, float2* F, float alpha) {
   a.v = v;
   a.F = F;
   a.u = s.u;
-  for (int b = 0; b < 3; ++b) {
-    a.sinv3[b] = s.sinv[b];
-    a.lam3[b] = s.lam[b];
-  }
+  for (int b = 0; b < 3; ++b) a.lam[b] = s.lam[b];
   a.nx = p->nx;
   a.ny = p->ny;
   a.nz = p->nz;

@@ -50,19 +50,18 @@ __device__ __forceinline__ double stretch_depth(int i, int n, int p) {
   return 0.0;
 }
 
-// 1/s and lambda = 1 - 1/s over an axis (each FP64 rounded to FP32 once: 1 minus the
-// rounded 1/s loses the real part of a small lambda, 6e-8 of 1, whole at a depth
-// where a^2 is less), one thread per voxel
-__global__ void k_scpml_stretch(int n, int pml, int order, double alpha, float2* sinv, float2* lam) {
+// lambda = 1 - 1/s over an axis, one thread per voxel, FP64 rounded to FP32 once (1
+// minus a rounded 1/s loses what of lambda is below 6e-8: its whole real part where
+// a^2 is less).  1/s is applied as 1 - lambda.
+__global__ void k_scpml_lambda(int n, int pml, int order, double alpha, float2* lam) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= n) return;
   const double u = stretch_depth(m, n, pml);
   double um = 1.0;
   for (int k = 0; k < order; ++k) um *= u;
-  const double a = alpha * um;   // s = 1 + i a, 1/s = (1 - i a) / (1 + a^2)
-  const double r = 1.0 / (1.0 + a * a);
-  sinv[m] = make_float2((float)r, (float)(-a * r));
-  lam[m] = make_float2((float)(a * a * r), (float)(a * r));
+  const double a = alpha * um;   // s = 1 + i a, lambda = (a^2 + i a) / (1 + a^2)
+  const double r = a / (1.0 + a * a);
+  lam[m] = make_float2((float)(a * r), (float)r);
 }
 
 // ---------------------------------------------------------------------------

@@ -25,7 +25,7 @@ struct ScAxis {
   const float2* v;      // phase 1: the field [3][nz][ny][nx]
   float2* F;            // result [3][nz][ny][nx]
   float2* u;            // T_b v_b of every axis b, [3][nz][ny][nx]
-  const float2 *sinv3[3], *lam3[3];   // 1/s and lambda = 1 - 1/s along x, y and z
+  const float2* lam[3]; // lambda = 1 - 1/s along x, y and z
   const float2* tw;     // the axis's twiddle table
   int nx, ny, nz;
   int axis;             // 0 = x, 1 = y, 2 = z
@@ -118,7 +118,7 @@ __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_apply(ScAxi
   const int tid = threadIdx.x;
   for (int i = tid; i < N; i += T) {
     tw[i] = a.tw[i];
-    lam[i] = a.lam3[a.axis][i];
+    lam[i] = a.lam[a.axis][i];
   }
   const int la = ROW ? tid / N2 : tid % TX, j2 = ROW ? tid % N2 : tid / TX;
   const int lb = ROW ? tid / N1 : tid % TX, k1 = ROW ? tid % N1 : tid / TX;
@@ -233,20 +233,20 @@ __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_apply(ScAxi
   }
 }
 
-// X = sum_b s_b^-1 u_b and Z = sum_b (s_b^-1 - 1) u_b = -sum_b lambda_b u_b, in place of u_x and u_y.
-// A launch of its own: accumulated in sc_apply X and Z would be read and written
-// by every axis, and formed in sc_grad from three fields they cost it its
-// occupancy (256 registers; 586 us against 246 for the x axis of 275 x 275 x 315).
+// Z = sum_b (s_b^-1 - 1) u_b = -sum_b lambda_b u_b and X = sum_b s_b^-1 u_b = Z +
+// sum_b u_b, in place of u_y and u_x.  A launch of its own: accumulated in sc_apply
+// X and Z would be read and written by every axis, and formed in sc_grad from three
+// fields they cost it its occupancy (256 registers; 586 us against 246 for the x
+// axis of 275 x 275 x 315).
 static __global__ void __launch_bounds__(256) sc_combine(ScAxis a) {
   const unsigned nvox = (unsigned)a.nx * a.ny * a.nz;
   float2 *u0 = a.u, *u1 = a.u + nvox, *u2 = u1 + nvox;
   for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < nvox; i += gridDim.x * 256) {
     const unsigned l = i / (unsigned)a.nx, x = i - l * a.nx, z = l / (unsigned)a.ny, y = l - z * a.ny;
     const float2 v0 = u0[i], v1 = u1[i], v2 = u2[i];
-    const float2 s0 = a.sinv3[0][x], s1 = a.sinv3[1][y], s2 = a.sinv3[2][z];
-    u0[i] = cadd(cmul(s0, v0), cadd(cmul(s1, v1), cmul(s2, v2)));
-    const float2 m0 = a.lam3[0][x], m1 = a.lam3[1][y], m2 = a.lam3[2][z];
-    u1[i] = cscale(cadd(cmul(m0, v0), cadd(cmul(m1, v1), cmul(m2, v2))), -1.0f);
+    const float2 m = cadd(cmul(a.lam[0][x], v0), cadd(cmul(a.lam[1][y], v1), cmul(a.lam[2][z], v2)));
+    u0[i] = csub(cadd(v0, cadd(v1, v2)), m);
+    u1[i] = make_float2(-m.x, -m.y);
   }
 }
 
@@ -260,7 +260,7 @@ __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_grad(ScAxis
   const int tid = threadIdx.x;
   for (int i = tid; i < N; i += T) {
     tw[i] = a.tw[i];
-    lam[i] = a.lam3[a.axis][i];
+    lam[i] = a.lam[a.axis][i];
   }
   const int la = ROW ? tid / N2 : tid % TX, j2 = ROW ? tid % N2 : tid / TX;
   const int lb = ROW ? tid / N1 : tid % TX, k1 = ROW ? tid % N1 : tid / TX;
