@@ -255,8 +255,9 @@ typedef struct {
 
 /* Device bytes of the stretched-layer workspace: restart + 1 basis fields, the
  * right-hand side, the stretched-derivative source, three scalar fields, the
- * stretch factors of each axis (n_a complex64) and reduction buffers.  0 if the
- * grid is not supported, an axis exceeds 1024 or restart is out of range. */
+ * stretch factors and 64-bit twiddles of each axis (3 n_a complex64) and reduction
+ * buffers.  0 if the grid is not supported, an axis exceeds 1024 or restart is out
+ * of range. */
 size_t cbs_scpml_workspace_bytes(int nx, int ny, int nz, int restart);
 
 /* Solve with the stretched layer.

@@ -1923,7 +1923,7 @@ int cbs_bandwidth_probe(const void* src, void* dst, size_t bytes, int reps, void
 namespace {
 
 struct ScpmlLayout {
-  size_t basis, b, F, u, lam[3], part, h, y, total;
+  size_t basis, b, F, u, lam[3], w64[3], part, h, y, total;
 };
 
 bool scpml_layout(int nx, int ny, int nz, int restart, ScpmlLayout& S) {
@@ -1943,6 +1943,7 @@ bool scpml_layout(int nx, int ny, int nz, int restart, ScpmlLayout& S) {
   S.F = take(3 * N * sizeof(float2));
   S.u = take(3 * N * sizeof(float2));
   for (int a = 0; a < 3; ++a) S.lam[a] = take((size_t)dims[a] * sizeof(float2));
+  for (int a = 0; a < 3; ++a) S.w64[a] = take((size_t)dims[a] * sizeof(double2));
   S.part = take((size_t)(kScpmlMaxRestart + 1) * kGmBlocks * sizeof(double2));
   S.h = take((size_t)3 * (kScpmlMaxRestart + 1) * sizeof(double2));
   S.y = take((size_t)(kScpmlMaxRestart + 1) * sizeof(double2));
@@ -1956,6 +1957,7 @@ struct Scpml {
   long long N, n3;            // voxels; complex values of a vector field
   float2 *basis, *b, *F, *u;
   const float2* lam[3];       // 1 - 1/s along each axis
+  const double2* w64[3];      // exp(-2 pi i m / n) of each axis
   double2 *part, *h, *y;
   float2* vec(int i) const { return basis + (long long)i * n3; }
 };
@@ -1993,8 +1995,10 @@ int scpml_setup(cbs_plan_s* p, const cbs_scpml* layer, int restart, void* work, 
     const int n = s.dims[a];
     float2* lam = reinterpret_cast<float2*>(base + S.lam[a]);
     s.lam[a] = lam;
+    double2* w64 = reinterpret_cast<double2*>(base + S.w64[a]);
+    s.w64[a] = w64;
     hipLaunchKernelGGL(k_scpml_lambda, dim3((n + 127) / 128), dim3(128), 0, p->stream, n, p->pml[a],
-                       layer->order, layer->alpha_max, lam);
+                       layer->order, layer->alpha_max, lam, w64);
     HIP_LAUNCHED();
   }
   return CBS_OK;
@@ -2034,6 +2038,7 @@ int enqueue_delta(const Scpml& s, const float2* v, float2* F, float alpha) {
       a.first = b == 0 ? 1 : 0;
       a.p = p->pml[b];
       a.tw = tw[b];
+      a.w64 = s.w64[b];
       launch[b](a, grad != 0, p->stream);
       HIP_LAUNCHED();
     }

@@ -93,104 +93,121 @@ constexpr int ct_first_radix(int n) {
 }
 
 // ---------------------------------------------------------------------------
-// complex helpers (float2 = re, im)
+// complex helpers, C = float2 or double2 (re, im)
 // ---------------------------------------------------------------------------
-CBS_HD float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
-CBS_HD float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
-CBS_HD float2 cmul(float2 a, float2 b) {
-  return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+template <class C>
+using real_t = std::conditional_t<std::is_same_v<C, double2>, double, float>;
+template <class C>
+CBS_HD C cmake(real_t<C> x, real_t<C> y) {
+  C r;
+  r.x = x;
+  r.y = y;
+  return r;
+}
+template <class C>
+CBS_HD C cadd(C a, C b) { return cmake<C>(a.x + b.x, a.y + b.y); }
+template <class C>
+CBS_HD C csub(C a, C b) { return cmake<C>(a.x - b.x, a.y - b.y); }
+template <class C>
+CBS_HD C cmul(C a, C b) {
+  return cmake<C>(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 // a * conj(b)
-CBS_HD float2 cmulc(float2 a, float2 b) {
-  return make_float2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
+template <class C>
+CBS_HD C cmulc(C a, C b) {
+  return cmake<C>(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
 }
 CBS_HD float2 cscale(float2 a, float s) { return make_float2(a.x * s, a.y * s); }
 
 // v * exp(2 pi i K / N), K a compile-time integer (any sign).
-template <int N, long long K>
-CBS_HD float2 rot(float2 v) {
+template <int N, long long K, class C>
+CBS_HD C rot(C v) {
+  using T = real_t<C>;
   constexpr long long k = ((K % N) + N) % N;
   if constexpr (k == 0) {
     return v;
   } else if constexpr (4 * k == N) {
-    return make_float2(-v.y, v.x);
+    return cmake<C>(-v.y, v.x);
   } else if constexpr (2 * k == N) {
-    return make_float2(-v.x, -v.y);
+    return cmake<C>(-v.x, -v.y);
   } else if constexpr (4 * k == 3 * N) {
-    return make_float2(v.y, -v.x);
+    return cmake<C>(v.y, -v.x);
   } else if constexpr (8 * k == N) {
-    constexpr float h = 0.70710678118654752440f;
-    return make_float2((v.x - v.y) * h, (v.x + v.y) * h);
+    constexpr T h = T(0.70710678118654752440);
+    return cmake<C>((v.x - v.y) * h, (v.x + v.y) * h);
   } else if constexpr (8 * k == 3 * N) {
-    constexpr float h = 0.70710678118654752440f;
-    return make_float2((-v.x - v.y) * h, (v.x - v.y) * h);
+    constexpr T h = T(0.70710678118654752440);
+    return cmake<C>((-v.x - v.y) * h, (v.x - v.y) * h);
   } else if constexpr (8 * k == 5 * N) {
-    constexpr float h = 0.70710678118654752440f;
-    return make_float2((v.y - v.x) * h, (-v.x - v.y) * h);
+    constexpr T h = T(0.70710678118654752440);
+    return cmake<C>((v.y - v.x) * h, (-v.x - v.y) * h);
   } else if constexpr (8 * k == 7 * N) {
-    constexpr float h = 0.70710678118654752440f;
-    return make_float2((v.x + v.y) * h, (v.y - v.x) * h);
+    constexpr T h = T(0.70710678118654752440);
+    return cmake<C>((v.x + v.y) * h, (v.y - v.x) * h);
   } else {
     constexpr CS w = ct_cis(k, N);
-    constexpr float c = float(w.c), s = float(w.s);
-    return make_float2(v.x * c - v.y * s, v.x * s + v.y * c);
+    constexpr T c = T(w.c), s = T(w.s);
+    return cmake<C>(v.x * c - v.y * s, v.x * s + v.y * c);
   }
 }
 
 // ---------------------------------------------------------------------------
 // codelets
 // ---------------------------------------------------------------------------
-template <int S>
-CBS_HD void dft3(float2& a0, float2& a1, float2& a2) {
-  constexpr float h = 0.86602540378443864676f;  // sin(2 pi / 3)
-  const float2 t1 = cadd(a1, a2);
-  const float2 t2 = make_float2(a0.x - 0.5f * t1.x, a0.y - 0.5f * t1.y);
-  const float2 d = csub(a1, a2);
+template <int S, class C>
+CBS_HD void dft3(C& a0, C& a1, C& a2) {
+  using T = real_t<C>;
+  constexpr T h = T(0.86602540378443864676);  // sin(2 pi / 3)
+  const C t1 = cadd(a1, a2);
+  const C t2 = cmake<C>(a0.x - T(0.5) * t1.x, a0.y - T(0.5) * t1.y);
+  const C d = csub(a1, a2);
   // i S h d
-  const float2 r = make_float2(-float(S) * h * d.y, float(S) * h * d.x);
+  const C r = cmake<C>(-T(S) * h * d.y, T(S) * h * d.x);
   a0 = cadd(a0, t1);
   a1 = cadd(t2, r);
   a2 = csub(t2, r);
 }
 
-template <int S>
-CBS_HD void dft4(float2& a0, float2& a1, float2& a2, float2& a3) {
-  const float2 t0 = cadd(a0, a2), t1 = csub(a0, a2);
-  const float2 t2 = cadd(a1, a3), d = csub(a1, a3);
-  const float2 t3 = make_float2(-float(S) * d.y, float(S) * d.x);  // (S i) d
+template <int S, class C>
+CBS_HD void dft4(C& a0, C& a1, C& a2, C& a3) {
+  using T = real_t<C>;
+  const C t0 = cadd(a0, a2), t1 = csub(a0, a2);
+  const C t2 = cadd(a1, a3), d = csub(a1, a3);
+  const C t3 = cmake<C>(-T(S) * d.y, T(S) * d.x);  // (S i) d
   a0 = cadd(t0, t2);
   a2 = csub(t0, t2);
   a1 = cadd(t1, t3);
   a3 = csub(t1, t3);
 }
 
-template <int P, int S>
-CBS_HD void dft_prime(float2 (&a)[P]) {
+template <int P, int S, class C>
+CBS_HD void dft_prime(C (&a)[P]) {
+  using T = real_t<C>;
   constexpr int H = (P - 1) / 2;
-  float2 sm[H], df[H];
+  C sm[H], df[H];
   sfor<1, H + 1>([&](auto J) {
     constexpr int j = CV(J);
     sm[j - 1] = cadd(a[j], a[P - j]);
     df[j - 1] = csub(a[j], a[P - j]);
   });
-  const float2 x0 = a[0];
-  float2 tot = x0;
+  const C x0 = a[0];
+  C tot = x0;
   sfor<0, H>([&](auto J) { tot = cadd(tot, sm[CV(J)]); });
   sfor<1, H + 1>([&](auto K) {
     constexpr int k = CV(K);
-    float2 A = x0, B = make_float2(0.f, 0.f);
+    C A = x0, B = cmake<C>(T(0), T(0));
     sfor<1, H + 1>([&](auto J) {
       constexpr int j = CV(J);
       constexpr CS w = ct_cis((long long)j * k, P);
-      constexpr float c = float(w.c), s = float(w.s);
+      constexpr T c = T(w.c), s = T(w.s);
       A.x += sm[j - 1].x * c;
       A.y += sm[j - 1].y * c;
       B.x += df[j - 1].x * s;
       B.y += df[j - 1].y * s;
     });
     // X_k = A + i S B, X_{P-k} = A - i S B
-    a[k] = make_float2(A.x - float(S) * B.y, A.y + float(S) * B.x);
-    a[P - k] = make_float2(A.x + float(S) * B.y, A.y - float(S) * B.x);
+    a[k] = cmake<C>(A.x - T(S) * B.y, A.y + T(S) * B.x);
+    a[P - k] = cmake<C>(A.x + T(S) * B.y, A.y - T(S) * B.x);
   });
   a[0] = tot;
 }
@@ -228,37 +245,38 @@ constexpr int ct_primitive_root(int p) {
 // (A +- B)/2 (two M x M products instead of four); the sine matrix is
 // [[A', B'], [-B', A']], taken as A'(v0 + v1) + (B' - A') v1 and
 // A'(v0 + v1) - (A' + B') v0 (three instead of four).
-template <int P, int S>
-CBS_HD void dft_prime_split(float2 (&a)[P]) {
+template <int P, int S, class C>
+CBS_HD void dft_prime_split(C (&a)[P]) {
+  using T = real_t<C>;
   constexpr int H = (P - 1) / 2;
   constexpr int M = H / 2;
   constexpr long long g = ct_primitive_root(P);
   constexpr long long ginv = ct_powmod(g, P - 2, P);
-  float2 pu[M], mu[M], v0[M], v1[M], vs[M];
+  C pu[M], mu[M], v0[M], v1[M], vs[M];
   sfor<0, M>([&](auto R0) {
     constexpr int r0 = CV(R0);
     constexpr int e0 = (int)ct_powmod(g, r0, P), e1 = (int)ct_powmod(g, r0 + M, P);
-    const float2 u0 = cadd(a[e0], a[P - e0]), u1 = cadd(a[e1], a[P - e1]);
+    const C u0 = cadd(a[e0], a[P - e0]), u1 = cadd(a[e1], a[P - e1]);
     v0[r0] = csub(a[e0], a[P - e0]);
     v1[r0] = csub(a[e1], a[P - e1]);
     pu[r0] = cadd(u0, u1);
     mu[r0] = csub(u0, u1);
     vs[r0] = cadd(v0[r0], v1[r0]);
   });
-  const float2 x0 = a[0];
-  float2 tot = x0;
+  const C x0 = a[0];
+  C tot = x0;
   sfor<0, M>([&](auto R0) { tot = cadd(tot, pu[CV(R0)]); });
   sfor<0, M>([&](auto Q0) {
     constexpr int q0 = CV(Q0);
-    float2 cp = x0, cm = make_float2(0.f, 0.f);
-    float2 k1 = make_float2(0.f, 0.f), k2 = k1, k3 = k1;
+    C cp = x0, cm = cmake<C>(T(0), T(0));
+    C k1 = cmake<C>(T(0), T(0)), k2 = k1, k3 = k1;
     sfor<0, M>([&](auto R0) {
       constexpr int r0 = CV(R0);
       constexpr int d = ((r0 - q0) % (2 * H) + 2 * H) % (2 * H);
       constexpr CS w0 = ct_cis(ct_powmod(g, d, P), P);
       constexpr CS w1 = ct_cis(ct_powmod(g, d + M, P), P);
-      constexpr float kp = float(0.5 * (w0.c + w1.c)), km = float(0.5 * (w0.c - w1.c));
-      constexpr float al = float(w0.s), bm = float(w1.s - w0.s), ap = float(w0.s + w1.s);
+      constexpr T kp = T(0.5 * (w0.c + w1.c)), km = T(0.5 * (w0.c - w1.c));
+      constexpr T al = T(w0.s), bm = T(w1.s - w0.s), ap = T(w0.s + w1.s);
       cp.x += kp * pu[r0].x;
       cp.y += kp * pu[r0].y;
       cm.x += km * mu[r0].x;
@@ -270,23 +288,23 @@ CBS_HD void dft_prime_split(float2 (&a)[P]) {
       k3.x += ap * v0[r0].x;
       k3.y += ap * v0[r0].y;
     });
-    const float2 At = cadd(cp, cm), Ab = csub(cp, cm);   // q = q0 and q = q0 + M
-    const float2 Bt = cadd(k1, k2), Bb = csub(k1, k3);
+    const C At = cadd(cp, cm), Ab = csub(cp, cm);   // q = q0 and q = q0 + M
+    const C Bt = cadd(k1, k2), Bb = csub(k1, k3);
     constexpr int ft = (int)ct_powmod(ginv, q0, P), fb = (int)ct_powmod(ginv, q0 + M, P);
-    a[ft] = make_float2(At.x - float(S) * Bt.y, At.y + float(S) * Bt.x);
-    a[P - ft] = make_float2(At.x + float(S) * Bt.y, At.y - float(S) * Bt.x);
-    a[fb] = make_float2(Ab.x - float(S) * Bb.y, Ab.y + float(S) * Bb.x);
-    a[P - fb] = make_float2(Ab.x + float(S) * Bb.y, Ab.y - float(S) * Bb.x);
+    a[ft] = cmake<C>(At.x - T(S) * Bt.y, At.y + T(S) * Bt.x);
+    a[P - ft] = cmake<C>(At.x + T(S) * Bt.y, At.y - T(S) * Bt.x);
+    a[fb] = cmake<C>(Ab.x - T(S) * Bb.y, Ab.y + T(S) * Bb.x);
+    a[P - fb] = cmake<C>(Ab.x + T(S) * Bb.y, Ab.y - T(S) * Bb.x);
   });
   a[0] = tot;
 }
 
-template <int N, int S>
-CBS_HD void dft(float2 (&a)[N]) {
+template <int N, int S, class C>
+CBS_HD void dft(C (&a)[N]) {
   static_assert(S == 1 || S == -1, "sign");
   if constexpr (N == 1) {
   } else if constexpr (N == 2) {
-    const float2 t = a[0];
+    const C t = a[0];
     a[0] = cadd(t, a[1]);
     a[1] = csub(t, a[1]);
   } else if constexpr (N == 3) {
@@ -301,10 +319,10 @@ CBS_HD void dft(float2 (&a)[N]) {
     // N = R * M; input index j = j2 + M j1, output index k = k1 + R k2.
     constexpr int R = ct_first_radix(N);
     constexpr int M = N / R;
-    float2 y[N];  // y[k1 * M + j2]
+    C y[N];  // y[k1 * M + j2]
     sfor<0, M>([&](auto J2) {
       constexpr int j2 = CV(J2);
-      float2 b[R];
+      C b[R];
       sfor<0, R>([&](auto J1) { b[CV(J1)] = a[j2 + M * CV(J1)]; });
       dft<R, S>(b);
       sfor<0, R>([&](auto K1) {
@@ -314,7 +332,7 @@ CBS_HD void dft(float2 (&a)[N]) {
     });
     sfor<0, R>([&](auto K1) {
       constexpr int k1 = CV(K1);
-      float2 c[M];
+      C c[M];
       sfor<0, M>([&](auto J2) { c[CV(J2)] = y[k1 * M + CV(J2)]; });
       dft<M, S>(c);
       sfor<0, M>([&](auto K2) { a[k1 + R * CV(K2)] = c[CV(K2)]; });

@@ -52,8 +52,10 @@ __device__ __forceinline__ double stretch_depth(int i, int n, int p) {
 
 // lambda = 1 - 1/s over an axis, one thread per voxel, FP64 rounded to FP32 once (1
 // minus a rounded 1/s loses what of lambda is below 6e-8: its whole real part where
-// a^2 is less).  1/s is applied as 1 - lambda.
-__global__ void k_scpml_lambda(int n, int pml, int order, double alpha, float2* lam) {
+// a^2 is less).  1/s is applied as 1 - lambda.  w64 = exp(-2 pi i m / n), the twiddles
+// of the 64-bit transform.
+__global__ void k_scpml_lambda(int n, int pml, int order, double alpha, float2* lam,
+                               double2* w64) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= n) return;
   const double u = stretch_depth(m, n, pml);
@@ -62,6 +64,9 @@ __global__ void k_scpml_lambda(int n, int pml, int order, double alpha, float2* 
   const double a = alpha * um;   // s = 1 + i a, lambda = (a^2 + i a) / (1 + a^2)
   const double r = a / (1.0 + a * a);
   lam[m] = make_float2((float)(a * r), (float)r);
+  double sn, cs;
+  sincospi(2.0 * m / n, &sn, &cs);
+  w64[m] = make_double2(cs, -sn);
 }
 
 // ---------------------------------------------------------------------------

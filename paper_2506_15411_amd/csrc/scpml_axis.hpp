@@ -13,10 +13,10 @@
 // registers of the level-B threads and every level writes where it read.
 // Vector work bounds them (five transforms per 104 bytes moved); components are
 // separate work-groups, since a loop over them keeps the tables of all three in
-// registers.  The operator at 275 x 275 x 315 takes 2.54 ms, dense matrix products
+// registers.  The operator at 275 x 275 x 315 takes 2.60 ms, dense matrix products
 // on the FP32 matrix cores 7.04 ms; at 64^3 89 us against 460; relative error
-// against FP64 2.0e-7 (6.4e-7) on noise and 3.0e-6 (2.6e-6) on a spherical wave at
-// lambda / 16.
+// against FP64 at 275 x 275 x 315 1.8e-7 (products 6.4e-7) on noise and 9.8e-7 (2.6e-6)
+// on a spherical wave at lambda / 16.
 #pragma once
 
 namespace cbs {
@@ -27,6 +27,7 @@ struct ScAxis {
   float2* u;            // T_b v_b of every axis b, [3][nz][ny][nx]
   const float2* lam[3]; // lambda = 1 - 1/s along x, y and z
   const float2* tw;     // the axis's twiddle table
+  const double2* w64;   // exp(-2 pi i m / n) of the axis, m < n, in 64 bits
   int nx, ny, nz;
   int axis;             // 0 = x, 1 = y, 2 = z
   int p;                // layer voxels per side
@@ -108,6 +109,23 @@ __device__ __forceinline__ void edge_in(float2 i0, float2 i1, float2* b) {
 }
 constexpr bool sc_thin(int n1, int n2, int p) { return n1 >= 5 && p <= n2; }
 
+// The forward transform of v is taken in 64 bits and rounded once between its
+// levels: the symbols p and p^2 multiply what is rounded there by up to 10, where a
+// smooth field has p^2 = 0.15 (lambda / 16), so this transform's round-off is most of
+// the operator's error on a wave.  Products of 64 bits issue at the rate of those of
+// 32 here and need no more registers at once than the later levels do.  Error against
+// FP64 on a spherical wave, 32 bits -> 64: 64^3 1.86e-6 -> 6.5e-7, 192 x 192 x 256
+// 1.98e-6 -> 6.6e-7, 275 x 275 x 315 2.99e-6 -> 9.8e-7 (dense matrix products: 1.03e-6,
+// 1.64e-6, 2.61e-6); operator at 275 x 275 x 315 2.57 -> 2.60 ms, a GMRES step 9.21 ->
+// 9.28, 189 x 189 x 121 1.633 -> 1.657.  This is level A, level B is in sc_apply.
+template <int N1>
+__device__ __forceinline__ void dft_wide(float2 (&b)[N1]) {
+  double2 d[N1];
+  sfor<0, N1>([&](auto J) { d[CV(J)] = make_double2(b[CV(J)].x, b[CV(J)].y); });
+  dft<N1, -1>(d);
+  sfor<0, N1>([&](auto J) { b[CV(J)] = make_float2((float)d[CV(J)].x, (float)d[CV(J)].y); });
+}
+
 // F_c (+)= alpha [A v_c for c != axis, B v_c for c = axis], u_axis = T v_axis
 template <int N1, int N2, bool ROW, bool THIN>
 __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_apply(ScAxis a) {
@@ -146,16 +164,24 @@ __global__ void __launch_bounds__((ScGeom<N1, N2, ROW>::THREADS)) sc_apply(ScAxi
     if (oka) sfor<0, N1>([&](auto J) { b[CV(J)] = sc_at(v, g0 + CV(J) * gs); });
     __syncthreads();   // the tables are in LDS
     if (oka) {
-      dft<N1, -1>(b);
-      sfor<0, N1>([&](auto K) { l1[pa + N2 * SP * CV(K)] = cmul(b[CV(K)], twt[CV(K)]); });
+      dft_wide<N1>(b);
+      sfor<0, N1>([&](auto K) { l1[pa + N2 * SP * CV(K)] = b[CV(K)]; });   // twiddled in level B
     }
   }
+  const double2 w1 = a.w64[k1 < N1 ? k1 : 0];
   __syncthreads();
   if (okb) {
     float2 w[N2], g[N2];
-    sfor<0, N2>([&](auto J) { w[CV(J)] = l1[pb + SP * CV(J)]; });
-    dft<N2, -1>(w);
+    double2 d[N2], r = w1;   // r = exp(-2 pi i J k1 / n)
+    sfor<0, N2>([&](auto J) {
+      const float2 f = l1[pb + SP * CV(J)];
+      d[CV(J)] = make_double2(f.x, f.y);
+      if constexpr (CV(J) > 0) d[CV(J)] = cmul(d[CV(J)], r);
+      if constexpr (CV(J) > 0 && CV(J) + 1 < N2) r = cmul(r, w1);
+    });
+    dft<N2, -1>(d);
     sfor<0, N2>([&](auto K) {
+      w[CV(K)] = make_float2((float)d[CV(K)].x, (float)d[CV(K)].y);
       const float q = sc_freq<N>(k1 + N1 * CV(K), own);
       g[CV(K)] = imul(q * (1.0f / N), w[CV(K)]);
       w[CV(K)] = cscale(w[CV(K)], -q * q * (1.0f / N));
