@@ -165,6 +165,9 @@ __device__ __forceinline__ void residual_finish(const double* part, int per_b, i
     __syncthreads();   // red is rewritten for the next illumination
   }
   if (threadIdx.x == 0) {
+    auto set_done = [&] {   // read by other blocks of the z pass meanwhile
+      __hip_atomic_store(&st->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     if (bad) eta = NAN;
     {
       const int it = st->iter + 1;
@@ -173,13 +176,13 @@ __device__ __forceinline__ void residual_finish(const double* part, int per_b, i
       if (st->record && it <= kHistCap) hist[it - 1] = eta;
       if (!isfinite(eta)) {
         st->status = 3;
-        st->done = 1;
+        set_done();
       } else if (eta <= st->tol) {
         st->status = 1;
-        st->done = 1;
+        set_done();
       } else if (it >= st->max_iter) {
         st->status = 2;
-        st->done = 1;
+        set_done();
       }
     }
   }
@@ -917,12 +920,12 @@ kz_pass(CbsArgs a) {
   constexpr int N = G::N;
   __shared__ float2 lds[3 * N * TX];
   __shared__ float2 tw[N];
-  const int done = a.st->done;
+  __shared__ int stop;
   // block 0 transforms nothing: it finishes the previous iteration's residual
   // (stream order: the x pass that wrote the partials has completed) beside the
   // columns of the others
   if (blockIdx.x == 0) {
-    if (done || !a.st->pending) return;
+    if (a.st->done || !a.st->pending) return;
     constexpr bool kFits = sizeof(lds) >= 2 * kResStreams * sizeof(double);
     if constexpr (kFits) {
       residual_finish<G::THREADS>(a.partials, a.k1_blocks, a.nb, a.st, a.hist,
@@ -934,7 +937,13 @@ kz_pass(CbsArgs a) {
     if (threadIdx.x == 0) a.st->pending = 0;
     return;
   }
+  // Block 0 may raise the stop flag while the others look at it, so a work-group
+  // takes one thread's reading of it: whole groups go on or leave.  Some columns of
+  // W are then transformed and some are not, and W is dead: the passes behind this
+  // one see the flag, E is whole, and a solve's prologue forms W anew.
   const int tid = threadIdx.x;
+  int flag = 0;
+  if (tid == 0) flag = __hip_atomic_load(&a.st->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   TwStage<N, G::THREADS> tws;
   tws.issue(a.twz, tid);
   const int xi = tid % TX;
@@ -973,9 +982,10 @@ kz_pass(CbsArgs a) {
   };
   load_a();
   asm volatile("" ::: "memory");   // the loads are issued before the flag is waited for
-  if (done) return;
+  if (tid == 0) stop = flag;
   tws.commit(tw, tid);
   __syncthreads();
+  if (stop) return;
   if (t < 3 * N2) {
     dft<N1, -1>(b);
     const float2* twt = tw + j2 * N1;
