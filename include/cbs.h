@@ -75,9 +75,10 @@ enum {
 typedef struct {
   double tol;          /* stop when ||E^(k+1) - E^(k)|| / ||E^(k+1)|| <= tol (FP64 norms) */
   int max_iter;        /* hard cap on iterations (>= 1)                                   */
-  int check_every;     /* host polls the device convergence flag every this many
-                          iterations (>= 1); iterations past convergence are skipped on
-                          the device, so this only trades host syncs for idle launches   */
+  int check_every;     /* the host looks at the device convergence flag after at most
+                          this many iterations (>= 1), sooner where the residual says
+                          that the end is near; iterations past convergence are skipped
+                          on the device, so this only trades host syncs for idle launches */
   unsigned flags;      /* CBS_WARM_START | CBS_RETURN_SCATTERED | CBS_RECORD_HISTORY      */
 } cbs_opts;
 

@@ -19,6 +19,7 @@
 
 #include "../../include/cbs.h"
 #include "kernels.hpp"
+#include "pace.hpp"
 #include "scpml.hpp"
 
 namespace cbs {
@@ -694,6 +695,7 @@ struct cbs_plan_s {
     bool plane;     // plane-wave source: E_inc is added at the end
     unsigned flags;
     int max_iter;
+    double tol;
     int enqueued;   // iterations enqueued so far
     int head, count;  // ring of outstanding quanta
     float ms;       // device time from begin to the quantum that stopped
@@ -918,13 +920,11 @@ void set_illuminations(const cbs_plan_s* p, CbsArgs& a, int nb) {
   a.k1_blocks = a.fused ? 3 * p->nz : p->k1_blocks;
 }
 
-// Grids on which a stopped solve's remaining launches cost more than the latency
-// they hide: their passes look at the stop flag before they load anything, and a
-// blocking solve keeps one quantum in flight instead of two.  A solve in us, small
-// form -> large form, to 1e-4 and for 40 iterations (quanta of 10): 64^3 3355 ->
-// 3482, 873 -> 913; 121 x 189 x 100 45700 -> 46110, 4125 -> 4210; 189 x 189 x 121
-// 154820 -> 155540, 7165 -> 7220; 192 x 192 x 256 179340 -> 178070, 17350 -> 17430;
-// 275 x 275 x 315 636170 -> 631700, 48620 -> 48720.
+// Grids whose x and y passes look at the stop flag before they load anything: on the
+// others the flag's latency costs more than a stopped solve's few remaining launches,
+// which read the volume for nothing.  Iteration in us, flag late -> first: 121 x 189 x
+// 100 105.0 -> 105.6, 189 x 189 x 121 180.7 -> 181.7; 192 x 192 x 256 solved to 1e-4,
+// 179.3 -> 178.1 ms.
 bool large_grid(const cbs_plan_s* p) {
   return (long long)p->nx * p->ny * p->nz > 6LL << 20;
 }
@@ -1077,6 +1077,7 @@ int begin_solve(cbs_plan_s* p, CbsArgs& a, const cbs_opts* o, const cbs_source* 
   A.plane = plane;
   A.flags = o->flags;
   A.max_iter = o->max_iter;
+  A.tol = o->tol;
   A.enqueued = 0;
   A.head = A.count = 0;
   A.ms = 0.f;
@@ -1165,23 +1166,27 @@ int end_solve(cbs_plan_s* p, cbs_stats* stats) {
   return CBS_NOT_CONVERGED;
 }
 
-// Blocking solve on top of the primitives: quanta of check_every iterations, two
-// of them in flight (one on large grids), so the device has work while the host
-// reads the state of the one before (a 64^3 iteration takes 20 us and a host
-// round trip about as long: 100 iterations 2.13 -> 2.05 ms, 40 iterations of 32^3
-// 0.54 -> 0.51).  A solve that meets tol leaves at most the second quantum's
-// launches, which return before they compute or write.
+// Blocking solve on top of the primitives: quanta of at most check_every iterations,
+// two of them in flight, so the device has work while the host reads the state of
+// the one before (a 64^3 iteration takes 20 us and a host round trip about as long:
+// 100 iterations 2.13 -> 2.05 ms, 40 iterations of 32^3 0.54 -> 0.51), and sized by
+// the residual so that a solve that meets tol leaves little behind (pace.hpp).
 int run_blocking(cbs_plan_s* p, int check_every, cbs_stats* stats) {
   auto& A = p->act;
-  const int ahead = large_grid(p) ? 1 : 2;
+  Pace pace(A.tol, check_every, (A.flags & CBS_WARM_START) != 0);
   int done = 0, rc = CBS_OK;
   while (!done) {
-    while (!rc && A.count < ahead && A.enqueued < A.max_iter) rc = advance_solve(p, check_every);
+    while (!rc && A.count < 2 && A.enqueued < A.max_iter) {
+      const int q = pace.next(A.enqueued - p->last.iter);
+      if (q == 0) break;
+      rc = advance_solve(p, q);
+    }
     if (!rc && A.count == 0) rc = fail(CBS_E_STATE, "the device did not stop at max_iter");
     if (rc) break;
     const hipError_t e = hipEventSynchronize(p->evq[A.head]);
     if (e != hipSuccess) rc = fail(CBS_E_HIP, "hipEventSynchronize: %s", hipGetErrorString(e));
     if (rc || (rc = poll_solve(p, &done))) break;
+    pace.read(p->last.iter, p->last.eta);
   }
   if (rc) {
     A.on = false;
@@ -1319,8 +1324,9 @@ int run_static(cbs_plan_s* p, CbsArgs& a, const cbs_opts* o, const cbs_source* s
   DevState hs;
   std::memset(&hs, 0, sizeof(hs));
   int enqueued = 0;
+  Pace pace(o->tol, o->check_every, a.warm != 0);
   for (;;) {
-    const int q = std::min(o->check_every, o->max_iter - enqueued);
+    const int q = std::min(pace.next(0), o->max_iter - enqueued);
     for (int i = 0; i < q; ++i)
       if (int rc = enqueue_iteration(p, a, enqueued + i + 1 >= o->max_iter)) return rc;
     enqueued += q;
@@ -1328,6 +1334,7 @@ int run_static(cbs_plan_s* p, CbsArgs& a, const cbs_opts* o, const cbs_source* s
     HIP_TRY(hipMemcpyAsync(&hs, p->state, sizeof(DevState), hipMemcpyDeviceToHost, p->stream));
     HIP_TRY(hipStreamSynchronize(p->stream));
     if (hs.done || enqueued >= o->max_iter) break;
+    pace.read(hs.iter, hs.eta);
   }
   if (a.src == SRC_PLANE && !(o->flags & CBS_RETURN_SCATTERED)) {
     hipLaunchKernelGGL(k_incident, dim3(2048), dim3(256), 0, p->stream, a, 1.0f);
@@ -1508,6 +1515,11 @@ int cbs_solve_begin(cbs_plan_t p, int adjoint, const void* E_fwd, const cbs_sour
   Kvec kv;
   int rc = prepare(p, adjoint, src, E_dev, o, a, kv);
   if (rc) return rc;
+  // The caller's quanta, several of them in flight, may stay behind a solve that meets
+  // tol: past the L2s' 32 MB a stopped pass looks before it reads.  Two quanta of 29
+  // (17) behind one iteration: 121 x 189 x 100 2.48 -> 0.80 ms, 189 x 189 x 121 2.50 ->
+  // 0.75, 128^3 (quanta of 31) 1.26 -> 0.89; their iterations 0 to 0.5% longer.
+  if (24LL * p->nxp * p->ny * p->nz > 32LL << 20) a.flag_first = a.z_first = 1;
   return begin_solve(p, a, o, src, adjoint ? E_fwd : nullptr, kv);
 }
 

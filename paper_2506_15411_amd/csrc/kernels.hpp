@@ -216,7 +216,8 @@ struct CbsArgs {
   int oblique;                  // some illumination has kx or ky != 0 (phx, phy not all 1)
   int k1_prio;                  // x-pass: raise wave priority for the load phase (set by launch_k1)
   int ky_prio;                  // y pass: the same (set by launch_ky)
-  int flag_first;               // wait for the stop flag before the first loads (large grids)
+  int flag_first;               // x and y pass: the stop flag before the first loads (large_grid)
+  int z_first;                  // host: z pass the same (cbs_solve_begin)
   double* hist;                 // residual history
   DevState* st;
   int src;                      // SrcKind
@@ -322,10 +323,11 @@ __device__ __forceinline__ unsigned xcd_remap(unsigned b, unsigned total) {
   return k * q + (k < r ? k : r) + j;
 }
 
-// The stop flag before the first loads, on large grids: in the x and y passes, not
-// in the z and plane passes, which the smallest grids run (64^3 iteration with the
-// test 19.7 us, without 19.1).  A load of its own: waiting for flag_first would
-// wait for the flag too if that were already in flight.
+// The stop flag before the first loads, on large grids and in solves the caller
+// advances: in the x and y passes here, in the z pass by a form of its own.  The plane
+// pass looks late whatever the size (128^3 iteration 78.6 us, with the flag first
+// 80.1; 100 x 100 x 64 30.8 and 31.7).  A load of its own: waiting for flag_first
+// would wait for the flag too if that were already in flight.
 __device__ __forceinline__ bool stop_first(const CbsArgs& a) {
   const bool stop = a.flag_first && a.st->done;
   asm volatile("" ::: "memory");
@@ -739,8 +741,8 @@ kxy_pass(CbsArgs a) {
         sfor<0, N1>([&](auto J) { b[CV(QQ)][CV(J)] = w[N2 * kBrick * CV(J)]; });
       }
     });
-    // On small grids (flag_first 0) the stop flag, read first, is waited for behind
-    // the issued loads, here and in the other passes: one round trip less per launch
+    // The stop flag, read first, is waited for behind the issued loads, here and, where
+    // it does not come first, in the other passes: one round trip less per launch
     // (16^3 iteration 8.5 -> 7.9 us, 32^3 10.9 -> 10.1, 64^3 19.5 -> 19.1).
     asm volatile("" ::: "memory");
     if (done) return;
@@ -913,7 +915,10 @@ kxy_pass(CbsArgs a) {
 // ---------------------------------------------------------------------------
 // KZ: FFT along z, Green's tensor, inverse FFT along z (3 components)
 // ---------------------------------------------------------------------------
-template <int N1, int N2, int TX>
+// FIRST: the stop flag before the loads (z_first), a form of its own: a solve that
+// leaves few launches behind does better without the wait (64^3 iteration 19.7 us,
+// without 19.1; z pass of 275 x 275 x 315 261 us, without 255).
+template <int N1, int N2, int TX, bool FIRST>
 __global__ void __launch_bounds__((ZGeom<N1, N2, TX>::THREADS))
 kz_pass(CbsArgs a) {
   using G = ZGeom<N1, N2, TX>;
@@ -944,6 +949,11 @@ kz_pass(CbsArgs a) {
   const int tid = threadIdx.x;
   int flag = 0;
   if (tid == 0) flag = __hip_atomic_load(&a.st->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if constexpr (FIRST) {
+    if (tid == 0) stop = flag;
+    __syncthreads();
+    if (stop) return;
+  }
   TwStage<N, G::THREADS> tws;
   tws.issue(a.twz, tid);
   const int xi = tid % TX;
@@ -982,10 +992,10 @@ kz_pass(CbsArgs a) {
   };
   load_a();
   asm volatile("" ::: "memory");   // the loads are issued before the flag is waited for
-  if (tid == 0) stop = flag;
+  if (!FIRST && tid == 0) stop = flag;
   tws.commit(tw, tid);
   __syncthreads();
-  if (stop) return;
+  if (!FIRST && stop) return;
   if (t < 3 * N2) {
     dft<N1, -1>(b);
     const float2* twt = tw + j2 * N1;
@@ -1217,7 +1227,10 @@ void launch_kz(const CbsArgs& a, hipStream_t s) {
   constexpr int TX = kz_tx_for(N1, N2);
   using G = ZGeom<N1, N2, TX>;
   dim3 grid((unsigned)((long long)(a.nxp / TX) * a.ny * a.nb) + 1);   // + the residual's block
-  hipLaunchKernelGGL((kz_pass<N1, N2, TX>), grid, dim3(G::THREADS), 0, s, a);
+  if (a.z_first)
+    hipLaunchKernelGGL((kz_pass<N1, N2, TX, true>), grid, dim3(G::THREADS), 0, s, a);
+  else
+    hipLaunchKernelGGL((kz_pass<N1, N2, TX, false>), grid, dim3(G::THREADS), 0, s, a);
 }
 
 template <int N1, int N2>
