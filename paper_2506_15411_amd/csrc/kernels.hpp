@@ -686,8 +686,14 @@ ky_pass(CbsArgs a) {
 // 12 x 8: 768 threads 34.5 us, 576 36.6; 121: 704 threads 61.5, 1024 79.5 with a
 // mostly empty second round).  Row pitch N + 8: rows then start 64 bytes apart in
 // the banks and stay 16-byte aligned (128: 56.2 us, N + 2 59.3, N + 1 65.3).
-// 512-thread groups are held to six waves per SIMD, so three planes share a CU
-// (64 x 64 x 256: 22.7 us against 26.9).  Iteration in us, three passes -> fused:
+// Where the LDS holds two planes or more and a thread has one round of tasks, six
+// waves per SIMD are asked for, 80 registers: the lengths up to 48 take that or less by
+// themselves, 64 = 8 x 8 takes 84 and then holds two planes a CU instead of three
+// (iteration of 64 x 64 x 256 42.2 -> 38.5 us, eight illuminations 273 -> 267, at 8
+// bytes of scratch; 64^3 equal).  A field source's operands are 5 registers more and
+// lose by it (64 x 64 x 32 16.05 -> 17.3 us, 64 x 64 x 256 43.2 -> 44.5), two rounds
+// (96 = 12 x 8) spill 140 bytes, and eight waves cost every length (48 x 48 x 256 with a
+// field 30.6 -> 36.3, 64 x 64 x 256 38.5 -> 45.9).  Iteration in us, three passes -> fused:
 // 16^3 14.5 -> 8.6, 32^3 16.4 -> 10.8, 64^3 29.5 -> 19.5, 96^3 52.6 -> 46.3,
 // 121^3 88.4 -> 82.3, 128^3 95.7 -> 77.7, 128 x 128 x 256 172.7 -> 133.
 template <int N1, int N2>
@@ -697,15 +703,20 @@ struct XYGeom {
   static constexpr int GX = (N + kBrick - 1) / kBrick;
   static constexpr int RA = (N * N2 + 1023) / 1024, RB = (N * N1 + 1023) / 1024;   // rounds
   static constexpr int THREADS = round64(cmax((N * N2 + RA - 1) / RA, (N * N1 + RB - 1) / RB));
-  static constexpr int WAVES = THREADS == 512 ? 6 : 1;   // per SIMD, at least
   static constexpr int QG = (GX * kBrick * N2 + THREADS - 1) / THREADS;   // columns x N2 tasks
   static constexpr int QA = (N * N2 + THREADS - 1) / THREADS;
   static constexpr int QB = (N * N1 + THREADS - 1) / THREADS;
+  static constexpr int FIT = 160 * 1024 / (8 * N * (P + 1));   // planes the LDS of a CU holds
+  // waves per SIMD, at least
+  static constexpr int waves(bool field) {
+    const int all = (FIT * (THREADS / 64) + 3) / 4;   // with every plane that fits
+    return FIT >= 2 && QB == 1 && !field ? (all < 6 ? all : 6) : 1;
+  }
 };
 // MODE as in K1: K1_ITER the whole iteration, K1_FWD (W from E and the source, x
 // and y forward) and K1_RES (y and x inverse, fout = -res_scale gamma (GW - E)) its halves.
 template <int N1, int N2, int MODE, int FORM>
-__global__ void __launch_bounds__((XYGeom<N1, N2>::THREADS), (XYGeom<N1, N2>::WAVES))
+__global__ void __launch_bounds__((XYGeom<N1, N2>::THREADS), (XYGeom<N1, N2>::waves(FORM == FORM_FIELD)))
 kxy_pass(CbsArgs a) {
   using G = XYGeom<N1, N2>;
   constexpr int N = G::N, P = G::P, T = G::THREADS;
