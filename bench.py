@@ -32,8 +32,14 @@ HBM_PEAK_GBS = 8000.0
 #   y/z passes read and write the 24 B field; the x pass reads GW, E_s (24 B
 #   each) and V0 (8 B) and writes E_s and the next W (24 B each).
 PASS_BYTES = {"ky_forward": 48, "kz_green": 48, "ky_inverse": 48, "kx_update": 104}
-ITER_BYTES = 248
-PASS_SOURCES = ["paper_2506_15411_amd/csrc/kernels.hpp", "paper_2506_15411_amd/csrc/codelets.hpp"]
+#   where a plane's three passes run as one kernel, that kernel moves what the x
+#   pass does (W in and out, E_s twice, V0); time_passes reports it in the x pass's
+#   place and the y passes as 0
+PLANE_BYTES = {"kz_green": 48, "plane": 104}
+# the kernels and, since a length's split is part of its kernels, the size tables
+PASS_SOURCES = ["paper_2506_15411_amd/csrc/" + f for f in
+                ("kernels.hpp", "codelets.hpp", "sizes_small.hip", "sizes_mid.hip",
+                 "sizes_large.hip")]
 
 
 def log(*a):
@@ -51,6 +57,39 @@ def kernel_hash() -> str:
         src = re.sub(r"//[^\n]*", " ", src)
         h.update(" ".join(src.split()).encode())
     return h.hexdigest()[:16]
+
+
+def pass_model(times: dict):
+    """The passes an iteration runs: (ms, algorithmic bytes per voxel) by name, from
+    Plan.time_passes, and the residual's ms."""
+    t = dict(times)
+    residual = t.pop("residual")
+    bytes_of = PASS_BYTES
+    if t["ky_forward"] == 0.0 and t["ky_inverse"] == 0.0:
+        t = {"kz_green": t["kz_green"], "plane": t["kx_update"]}
+        bytes_of = PLANE_BYTES
+    return {k: (ms, bytes_of[k]) for k, ms in t.items()}, residual
+
+
+def iteration_figures(times: dict, nvox: int, traffic_of) -> dict:
+    """The JSON entries of an iteration: its time and share of the HBM peak, every
+    pass's time, and the roofline of the longest (traffic_of: its measured bytes)."""
+    passes, residual = pass_model(times)
+    it_ms = sum(ms for ms, _ in passes.values()) + residual
+    dom = max(passes, key=lambda k: passes[k][0])
+    ms, nbytes = passes[dom]
+    achieved = nbytes * nvox / (ms * 1e-3) / 1e9
+    moved = sum(b for _, b in passes.values())
+    return {
+        "hbm_frac_iteration": round(moved * nvox / (it_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
+        "iteration_ms": round(it_ms, 4),
+        "passes_ms": {**{k: round(v, 4) for k, (v, _) in passes.items()},
+                      "residual": round(residual, 4)},
+        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
+                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
+                     "traffic": traffic_of(dom), "kernel": dom,
+                     "alg_bytes_per_launch": nbytes * nvox, "avg_launch_ms": round(ms, 4)},
+    }
 
 
 def workload(name: str):
@@ -235,10 +274,8 @@ def design_bench(args, dev):
     dt = time.perf_counter() - t0
     end = figures()
     log(f"[bench] design end: {end}")
-    passes = opt.plan.time_passes(iters=10)
-    it_ms = sum(passes.values())
-    dom = max(PASS_BYTES, key=lambda k: passes[k])
-    achieved = PASS_BYTES[dom] * nvox / (passes[dom] * 1e-3) / 1e9
+    figs = iteration_figures(opt.plan.time_passes(iters=10), nvox,
+                             lambda kernel: traffic_from_profile("lens32", kernel))
     opt.close()
     k = max(1, args.steps)
     out = {
@@ -252,14 +289,7 @@ def design_bench(args, dev):
                                f"NA 0.84 n = 1.54",
                    "voxels": nvox, "smoothing": not args.no_smoothing, "tol": args.tol,
                    "iterations_per_step": iters / k},
-        "hbm_frac_iteration": round(ITER_BYTES * nvox / (it_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-        "iteration_ms": round(it_ms, 4),
-        "passes_ms": {kk: round(v, 4) for kk, v in passes.items()},
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": traffic_from_profile("lens32", dom),
-                     "kernel": dom, "alg_bytes_per_launch": PASS_BYTES[dom] * nvox,
-                     "avg_launch_ms": round(passes[dom], 4)},
+        **figs,
         "design": {"fom_relative": [round(f / foms[0], 4) for f in foms],
                    "lens_start": start, "lens_end": end,
                    "paper_context_s_per_step": 3.7},
@@ -458,15 +488,8 @@ def main(argv=None):
     # per-pass device time (HIP events on the plan's stream)
     passes = plan.time_passes(iters=10)
     log(f"[bench] passes (ms): {passes}")
-    dom = max(PASS_BYTES, key=lambda k: passes[k])
-    achieved = PASS_BYTES[dom] * nvox / (passes[dom] * 1e-3) / 1e9
-    traffic = traffic_from_profile(args.workload, dom)
-    roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                "traffic": traffic, "kernel": dom,
-                "alg_bytes_per_launch": PASS_BYTES[dom] * nvox,
-                "avg_launch_ms": round(passes[dom], 4)}
-    it_ms = sum(passes.values())
+    figs = iteration_figures(passes, nvox,
+                             lambda kernel: traffic_from_profile(args.workload, kernel))
     copy_ms = copy_probe(dev, reps=5)
     copy_gbs = 2 * (1 << 30) / (copy_ms * 1e-3) / 1e9
     out = {
@@ -480,12 +503,9 @@ def main(argv=None):
                    "voxels": nvox, "iterations_per_step": iters / args.steps,
                    "tol": args.tol, "shift_factor": plan_kappa, "pml_per_side": list(sc.pml),
                    "pml_order": plan_order, "sigma_max": plan_sigma},
-        "hbm_frac_iteration": round(ITER_BYTES * nvox / (it_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-        "iteration_ms": round(it_ms, 3),
+        **figs,
         "solve_only_gvoxel_iter_s": round(iter_rate, 3),
-        "passes_ms": {k: round(v, 4) for k, v in passes.items()},
         "copy_probe_gbs": round(copy_gbs, 1),
-        "roofline": roofline,
         "serving": None,
         "cpu_baseline": None,
     }

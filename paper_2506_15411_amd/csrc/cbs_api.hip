@@ -1891,7 +1891,7 @@ int cbs_time_passes(cbs_plan_t p, void* E_dev, int iters, float* ms_out) {
     for (int k = 0; k < 5; ++k) {
       float ms = 0.f;
       HIP_TRY(hipEventElapsedTime(&ms, p->evp[k], p->evp[k + 1]));
-      acc[kSlot[k]] += ms;
+      if (!(a.fused && (kSlot[k] == 0 || kSlot[k] == 2))) acc[kSlot[k]] += ms;   // no y launch: 0
     }
   }
   for (int k = 0; k < 5; ++k) ms_out[k] = (float)(acc[k] / iters);
