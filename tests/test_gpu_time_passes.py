@@ -1,5 +1,5 @@
-"""Plan.time_passes tells the fused plane pass from the four passes (GPU): where no y
-pass is launched its time is exactly 0."""
+"""Plan.time_passes tells the fused plane pass from the four passes (GPU): what is
+not launched, the plane's y passes and the residual's own launch, has a time of 0."""
 
 import pytest
 import torch
@@ -18,5 +18,6 @@ def test_y_entries(shape, fused, device):
     p.set_permittivity(eps)
     t = p.time_passes(iters=3)
     assert (t["ky_forward"] == 0.0 and t["ky_inverse"] == 0.0) == fused
+    assert t["residual"] == 0.0   # reduced inside the next z pass
     assert t["kz_green"] > 0.0 and t["kx_update"] > 0.0
     p.close()
