@@ -19,7 +19,10 @@ namespace cbs {
 // 0.3 ms and 0.06, and the warm start takes 0.61 ms.
 class Pace {
  public:
-  Pace(double tol, int check_every, bool warm) : tol_(tol), every_(check_every), warm_(warm) {
+  // long_iter: an iteration takes longer than the host's reading of one
+  Pace(double tol, int check_every, bool warm, bool long_iter)
+      : tol_(tol), every_(check_every), quarter_(std::max(1, check_every / 4)),
+        least_(long_iter ? 1 : quarter_), warm_(warm) {
     if (!(tol > 0.0)) left_ = INFINITY;
   }
   // the residual eta after iteration iter, as the host reads it
@@ -32,19 +35,18 @@ class Pace {
     }
   }
   // iterations to enqueue next when `ahead` of them are in flight past the last that
-  // was read (none: something has to be enqueued); 0: wait.  Less than a quarter of
-  // a quantum is not worth a read of its own.
+  // was read (none: something has to be enqueued); 0: wait.  Where iterations are as
+  // short as a reading, less than a quarter of a quantum is not worth one.
   int next(int ahead) const {
-    const int least = std::max(1, every_ / 4);
-    if (left_ < 0.0) return ahead ? 0 : warm_ ? std::min(every_, least) : every_;
+    if (left_ < 0.0) return ahead ? 0 : warm_ ? quarter_ : every_;
     const double q = std::min((double)every_, std::ceil(left_) - ahead);
-    if (q >= least) return (int)q;
-    return ahead ? 0 : std::min(every_, least);
+    if (q >= least_) return (int)q;
+    return ahead ? 0 : least_;
   }
 
  private:
   double tol_;
-  int every_;
+  int every_, quarter_, least_;
   bool warm_;
   int iter_ = 0;
   double eta_ = 0.0;

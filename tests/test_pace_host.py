@@ -16,11 +16,11 @@ HARNESS = r"""
 #include <cstdio>
 #include <cstdlib>
 #include <deque>
-// args: tol every warm eta1 rate max_iter; prints iterations done, enqueued, reads
+// args: tol every warm eta1 rate max_iter long_iter; prints iterations done, enqueued, reads
 int main(int, char** v) {
   const double tol = atof(v[1]), eta1 = atof(v[4]), rate = atof(v[5]);
   const int every = atoi(v[2]), warm = atoi(v[3]), max_iter = atoi(v[6]);
-  cbs::Pace pace(tol, every, warm != 0);
+  cbs::Pace pace(tol, every, warm != 0, atoi(v[7]) != 0);
   std::deque<int> flight;   // last iteration of each quantum in flight
   int enqueued = 0, read = 0, reads = 0, done = 0, iter = 0;
   double eta = eta1 / rate;
@@ -60,9 +60,10 @@ def pace(tmp_path_factory):
                         str(d / "h.cpp"), "-o", str(d / "h")], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
 
-    def run(tol, every, warm, eta1, rate, max_iter=100000):
+    def run(tol, every, warm, eta1, rate, max_iter=100000, long_iter=False):
         r = subprocess.run([str(d / "h"), repr(tol), str(every), str(int(warm)), repr(eta1),
-                            repr(rate), str(max_iter)], capture_output=True, text=True)
+                            repr(rate), str(max_iter), str(int(long_iter))],
+                           capture_output=True, text=True)
         assert r.returncode == 0, r.returncode
         return tuple(int(x) for x in r.stdout.split())
     return run
@@ -83,6 +84,19 @@ def test_converging_solves_leave_little_behind(pace, every, n, warm):
     assert enqueued - n < (every if not warm and n <= unknown else least + 1)
     # a quantum stays check_every iterations long while the end is far
     assert reads <= -(-n // every) + (5 if n > unknown else 3)
+
+
+@pytest.mark.parametrize("every", [1, 10, 20, 64])
+@pytest.mark.parametrize("n", [45, 63, 150, 160, 871])
+def test_long_iterations_end_on_the_spot(pace, every, n):
+    """Where an iteration outlasts a reading the last ones are enqueued one by one:
+    at most one behind a steady residual, and few reads for it."""
+    if n <= 2 * every:
+        pytest.skip("fewer than two residuals read")
+    rate = 1e-4 ** (1.0 / n) * 0.999999
+    done, enqueued, reads = pace(1e-4, every, False, rate, rate, long_iter=True)
+    assert done == n and enqueued - n <= 1
+    assert reads <= -(-n // every) + 3
 
 
 @pytest.mark.parametrize("tol,rate", [(0.0, 0.9), (0.0, 1.0), (1e-4, 1.0), (1e-4, 1.001)])
