@@ -243,13 +243,17 @@ constexpr int round64(int t) { return (t + 63) / 64 * 64; }
 // takes the R <= 8 with the least vector work per row, the waves of each level
 // weighed by its operation count (an n-point codelet about n times the sum of
 // its prime factors, the update about 25 per element), the larger R (longer
-// pieces of W) on ties.  Workgroups are at most four waves; two where a thread
-// holds more than about 160 registers (two waves per SIMD), since a larger
-// group then leaves part of the CU empty.  Measured on these splits, x pass in
-// us (rows: time):
-// 189 = 27 x 7: 4: 99, 5: 110, 6: 96, 7: 87, 8: 96; 315 = 35 x 9: 3: 262, 5: 241,
-// 7: 226, 8: 478; 275 = 25 x 11: 4: 574, 5: 537, 7: 576; 261 = 29 x 9:
-// 4: 166, 7: 175; 621 = 27 x 23 (198 registers): 4: 605, 7: 640, 8: 627.
+// pieces of W) on ties.  Workgroups are at most four waves; two where the estimate of
+// a thread's registers is above 160, since with two waves per SIMD a larger group
+// leaves part of the CU empty (621 = 27 x 23, 193 registers; 261 = 29 x 9 is estimated
+// at 170 and holds 132).  Measured on these splits, x pass of n x n x 64 (621: 100
+// rows) in us, rows: time, the rule's choice first:
+// 96 = 12 x 8: 5: 15.8, 8: 15.9, 4: 16.6; 100 = 10 x 10: 6: 16.8, 5: 17.2, 8: 18.6;
+// 121 = 11 x 11: 5: 21.6, 4: 23.2, 6: 26.3; 128 = 16 x 8: 8: 20.6, 7: 21.3, 5: 23.4;
+// 189 = 21 x 9: 6: 41.4, 7: 41.8, 8: 43.0; 192 = 16 x 12: 8: 40.6, 4: 40.8, 5: 42.3;
+// 256 = 16 x 16: 8: 68.6, 4: 68.6, 5: 74.6; 261: 4: 93.2, 6: 90.2, 8: 93.7, 5: 103;
+// 275 = 25 x 11: 5: 106.8, 7: 110.9, 6: 115; 315 = 21 x 15: 8: 131.7, 3: 129.4, 5: 139;
+// 621: 4: 80.7, 8: 84.3, 7: 91.4, 5: 104.
 constexpr int codelet_ops(int n) {
   int ops = 0, m = n;
   for (int p = 2; m > 1; ++p)
@@ -681,7 +685,10 @@ ky_pass(CbsArgs a) {
 //
 // One plane is one CU's work, and its time is the latency of seven dependent
 // levels (about 13 us at 64 x 64, 24 at 128 x 128), bounded by vector
-// instructions there (16 us of issue at 128 x 128).  Threads: as few as keep the
+// instructions there (16 us of issue at 128 x 128).  The operands of the update are
+// loaded behind the first level and held through the next two: the iteration form
+// spills 8 (12 oblique) bytes a lane at 64 x 64, 32, 40 and 112 with a field at 121 x
+// 121, 20, 36 and 128 at 128 x 128, none at the other lengths.  Threads: as few as keep the
 // rounds of 1024 threads over the N N2 and N N1 tasks of the two levels (96 =
 // 12 x 8: 768 threads 34.5 us, 576 36.6; 121: 704 threads 61.5, 1024 79.5 with a
 // mostly empty second round).  Row pitch N + 8: rows then start 64 bytes apart in

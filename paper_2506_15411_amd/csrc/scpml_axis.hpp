@@ -37,7 +37,8 @@ struct ScAxis {
 
 // Lines per work-group: eight, whose two exchange buffers leave room for four
 // work-groups per CU at 275 points (16 columns, two work-groups: y axis of 275 x
-// 275 x 315 885 us against 760), four on axes above about 600.
+// 275 x 315 885 us against 760 in the whole-transform form), four on axes above
+// about 600.
 template <int N1, int N2, bool ROW>
 struct ScGeom {
   static constexpr int N = N1 * N2;
@@ -93,7 +94,7 @@ __device__ __forceinline__ float2 imul(float q, float2 v) { return make_float2(-
 // only, and lambda D v is zero elsewhere.  The inverse DFT-N1 for those two
 // outputs, and the forward one of those two inputs, are sums of N1 terms, a third
 // of the work of a DFT-25 (275 x 275 x 315, layers of 8: x axis 630 -> 457 us, y
-// axis 760 -> 573; four edge elements or more a side would cost what the full
+// axis 760 -> 573, before the first transform went to 64 bits: 510 and 612; four edge elements or more a side would cost what the full
 // transform does, the 48-voxel z layer keeps it).
 template <int N1>
 __device__ __forceinline__ void edge_out(const float2* b, float2& o0, float2& o1) {
