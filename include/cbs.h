@@ -176,7 +176,8 @@ int cbs_adjoint_solve(cbs_plan_t plan, const void* E_fwd_dev, const cbs_source* 
  *
  * Begin a forward (adjoint = 0; arguments as cbs_solve) or adjoint (adjoint = 1;
  * arguments as cbs_adjoint_solve) solve: validates, initialises the device state
- * and enqueues the prologue. */
+ * and enqueues the prologue.  A source field is the solve's until it has stopped:
+ * its iterations read it, but not again the rows that the prologue found all zero. */
 int cbs_solve_begin(cbs_plan_t plan, int adjoint, const void* E_fwd_dev, const cbs_source* src,
                     void* E_dev, const cbs_opts* opts);
 
